@@ -207,12 +207,11 @@ WeightPlan plan_weights(const dlm_config& c) {
 // Workspace carve-up for one (B, P, D).
 struct Workspace {
     size_t total = 0;
-    size_t x, h, q, k, v, attn, rope, hf, ids, wts, grp_off, tile_tab,
+    size_t x, h, q, k, v, attn, rope, hf, ids, wts, grp_off,
         n_tiles, slot, a_rows, ecount, hexp, y, hfin, partials, top1, conf, maxlogit, counters, tokens;
-    int rows_total = 0, max_tiles = 0, n_vtiles = 0;
+    int rows_total = 0, n_vtiles = 0;
 };
 
-constexpr int kExpertBM = 256, kExpertBN = 256;
 constexpr int kHeadBM = 256, kHeadBN = 256;
 
 Workspace plan_workspace(const dlm_config& c, int B, int P, int D) {
@@ -236,11 +235,9 @@ Workspace plan_workspace(const dlm_config& c, int B, int P, int D) {
     } else {
         const int E = c.n_experts, k = c.top_k, G = E + c.n_shared_experts;
         w.rows_total = (int)(T * k + T * c.n_shared_experts);
-        w.max_tiles = (w.rows_total + kExpertBM - 1) / kExpertBM + G;
         w.ids = add(T * k * 4);
         w.wts = add(T * k * 4);
         w.grp_off = add((G + 1) * 4);
-        w.tile_tab = add((int64_t)w.max_tiles * 8);
         w.n_tiles = add(4);
         w.slot = add(T * k * 4);
         w.a_rows = add((int64_t)w.rows_total * 4);
@@ -391,6 +388,72 @@ GemmArgs gemm_args(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
     return a;
 }
 
+// Tile of a dense product with M x N outputs of K products each.  The
+// ping-pong 256x256 tiles are the best per tile, but each is a CU's whole work
+// for a while: they are taken when their rounds over the 256 CUs are at least
+// three quarters full.  Below that, tiles of a quarter and a sixteenth of the
+// size, as many as two (or three) workgroups per CU hold at once.
+struct GemmTile {
+    int bm, bn, variant;
+};
+
+int64_t tiles_of(int64_t M, int64_t N, int bm, int bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn); }
+
+bool big_tiles_fill(int64_t M, int64_t N, int64_t K, double least) {
+    const int64_t n = tiles_of(M, N, 256, 256);
+    return K >= 2048 && n >= least * 256 * ((n + 255) / 256);
+}
+
+// Residual products (O, dense down), us with the launch, at d = K = 2048:
+// 512 rows (256 tiles of 64x64) 15.2 on 64x64 with five stages, 21.0 on 128x64,
+// 31.4 before; 1263 rows (640) 28.2 on 64x64 with three stages, 30.2 on 64x128,
+// 43.1 before; 2048 rows (1024) 30.6 on 128x128, 35.3 on 64x128, 37.2 before;
+// 5120 rows: 160 big tiles 59.7, 128x128 56.4; 8192 rows: 256 big tiles 74.4,
+// 128x128 78.3; 10240 rows: 320 big tiles 112, 128x128 92.6.  At K = 1024 a big
+// tile's epilogue weighs too much: 16384 rows (256 big tiles) 51.8 against 47.2.
+GemmTile resid_tile(int64_t M, int64_t N, int64_t K) {
+    if (big_tiles_fill(M, N, K, 0.8)) return {256, 256, 11};
+    const int64_t n = tiles_of(M, N, 64, 64);
+    if (n <= 512) return {64, 64, 3};
+    if (n <= 768) return {64, 64, 4};
+    return {128, 128, 3};
+}
+
+// QKV (M = features, N = tokens): d = 2048, 3072 features: 512 tokens (192
+// tiles of 128x64) 21.6, on 128x128 26.8, 256x128 (before) 40.9; 1263 (480)
+// 28.8 / 28.4 / 42.8; 2048 (768) 43.1 / 38.8 / 43.7; 6144 (288 big tiles) 106
+// against 88.1 on 128x128; 4096 (192 big) 58.5 against 60.6; 10240 (480 big)
+// 120 against 145.  With 4096-long rows 128x128 is ahead sooner: 512 tokens
+// (384 tiles of 128x64) 52.0 / 45.5 / 68.5.
+GemmTile qkv_tile(int64_t M, int64_t N, int64_t K) {
+    if (big_tiles_fill(M, N, K, 0.75)) return {256, 256, 11};
+    return tiles_of(M, N, 128, 64) <= (K < 4096 ? 512 : 256) ? GemmTile{128, 64, 3} : GemmTile{128, 128, 4};
+}
+
+// Gate/up of the dense FFN: M rows, N interleaved gate and up columns.
+GemmTile gate_up_tile(int64_t M, int64_t N, int64_t K) {
+    if (big_tiles_fill(M, N, K, 0.75)) return {256, 256, 11};
+    return tiles_of(M, N, 64, 128) <= 512 ? GemmTile{64, 128, 3} : GemmTile{128, 128, 3};
+}
+
+// Expert products of T tokens: what counts is the rows that an expert gets on
+// average.  gate/up + down, us, at d 2048, 64 experts of 1024, top 8: 12 rows
+// each 117 + 57 on 64x128, 144 + 63 on 128x128, 162 + 75 on the big tiles; 64
+// rows 137 + 68 / 144 + 68 / 169 + 81; 80 rows 147 + 77 / 145 + 70 / 168 + 81;
+// 128 rows - / 161 + 88 / 167 + 88; 158 rows - / 179 + 100 / 179 + 92.  An
+// expert with more than 64 rows takes its weights twice with 64-row tiles:
+// with 257 groups of 25 MB (d 4096) that costs more than the finer split gains
+// (64 rows: 1438 + 790 / 1244 + 702 / 1237 + 689), so from 40 rows on only
+// where the tiles are too few to even out (twice the resident workgroups).
+GemmTile expert_tile(const dlm_config& c, int64_t T) {
+    const int64_t G = c.n_experts + c.n_shared_experts;
+    const double rows = (double)T * c.top_k / c.n_experts;
+    const int64_t narrow = G * ((2 * (int64_t)c.expert_ffn_dim + 127) / 128);
+    if (rows <= 40 || (rows <= 72 && narrow <= 2048)) return {64, 128, 3};
+    if (rows <= 128) return {128, 128, 3};
+    return {256, 256, 11};
+}
+
 #define TRY(expr)                        \
     do {                                 \
         dlm_status _s = (expr);          \
@@ -426,9 +489,9 @@ dlm_status run_layer(Ctx& x, int l) {
         a.n_heads = H;
         a.n_kv = KV;
         a.head_dim = hd;
-        const int64_t big_tiles = (int64_t)((N + 255) / 256) * ((x.T + 255) / 256);
-        a.variant = big_tiles >= 192 ? 11 : 0;          // ping-pong 8-wave 256x256 tiles
-        TRY(gemm(x, "gemm_qkv", a, EPI_QKV, false, 256, a.variant != 0 ? 256 : 128, 0));
+        const GemmTile t = qkv_tile(N, x.T, d);
+        a.variant = t.variant;
+        TRY(gemm(x, "gemm_qkv", a, EPI_QKV, false, t.bm, t.bn, 0));
     }
     if (x.kv_only && l + 1 == c.n_layers) return DLM_OK;    // the cache holds this window's K/V now
     {
@@ -442,12 +505,9 @@ dlm_status run_layer(Ctx& x, int l) {
         GemmArgs a = gemm_args(attn, (int64_t)H * hd, x.wt(L.wo), (int64_t)H * hd, x.T, d, H * hd);
         a.out = xs;
         a.ldo = d;
-        const int64_t big_tiles = (int64_t)((x.T + 255) / 256) * ((d + 255) / 256);
-        a.variant = big_tiles >= 128 ? 11 : 0;
-        // up to 1024 rows (drafting windows): 128 x 64 tiles, twice the workgroups of 128 x 128
-        const int obm = a.variant != 0 || x.T >= 4096 ? 256 : 128;
-        const int obn = a.variant != 0 ? 256 : x.T <= 1024 ? 64 : 128;
-        TRY(gemm(x, "gemm_o", a, EPI_RESID, false, obm, obn, 0));
+        const GemmTile t = resid_tile(x.T, d, H * hd);
+        a.variant = t.variant;
+        TRY(gemm(x, "gemm_o", a, EPI_RESID, false, t.bm, t.bn, 0));
     }
     // MoE FFN of the last block on the draft rows only (rows in [B][D] order)
     const bool draft_ffn = x.draft_rows_last_ffn && l + 1 == c.n_layers && c.n_experts > 0 && x.P > 0;
@@ -462,18 +522,28 @@ dlm_status run_layer(Ctx& x, int l) {
         GemmArgs a = gemm_args(h, d, x.wt(L.wgu), d, x.T, 2 * F, d);
         a.out = hf;
         a.ldo = F;
-        TRY(gemm(x, "gemm_ffn_gate_up", a, EPI_SWIGLU, false, x.T >= 4096 ? 256 : 128, 256, 0));
+        const GemmTile tg = gate_up_tile(x.T, 2 * F, d);
+        a.variant = tg.variant;
+        TRY(gemm(x, "gemm_ffn_gate_up", a, EPI_SWIGLU, false, tg.bm, tg.bn, 0));
         GemmArgs b = gemm_args(hf, F, x.wt(L.wd), F, x.T, d, F);
         b.out = xs;
         b.ldo = d;
-        TRY(gemm(x, "gemm_ffn_down", b, EPI_RESID, false, x.T >= 4096 ? 256 : 128, 128, 0));
+        const GemmTile td = resid_tile(x.T, d, F);
+        b.variant = td.variant;
+        TRY(gemm(x, "gemm_ffn_down", b, EPI_RESID, false, td.bm, td.bn, 0));
         return DLM_OK;
     }
     const int E = c.n_experts, kk = c.top_k, NS = c.n_shared_experts, F = c.expert_ffn_dim;
     int32_t* ids = x.at<int32_t>(x.w.ids);
     float* wts = x.at<float>(x.w.wts);
     int32_t* grp_off = x.at<int32_t>(x.w.grp_off);
-    int2* tile_tab = x.at<int2>(x.w.tile_tab);
+    // The tile table lies in the attention output's buffer, which is free from
+    // the O projection to the next block's attention: at most one 8-byte entry
+    // per row of the experts (9 per token) against 256 bytes or more per token.
+    int2* tile_tab = x.at<int2>(x.w.attn);
+    const GemmTile et = expert_tile(c, Tf);
+    const int rows_total = Tf * (kk + NS);
+    const int max_tiles = std::min(rows_total, rows_total / et.bm + E + NS);
     int32_t* n_tiles = x.at<int32_t>(x.w.n_tiles);
     int32_t* slot = x.at<int32_t>(x.w.slot);
     int32_t* a_rows = x.at<int32_t>(x.w.a_rows);
@@ -487,7 +557,7 @@ dlm_status run_layer(Ctx& x, int l) {
         prof_end(x, "router_topk");
         if (e != hipSuccess) return fail(DLM_ERR_HIP, std::string("router_topk: ") + hipGetErrorString(e));
         prof_begin(x, "dispatch");
-        e = launch_dispatch(ids, Tf, kk, E, NS, kExpertBM, wg_counts, grp_off, tile_tab, n_tiles, slot, a_rows,
+        e = launch_dispatch(ids, Tf, kk, E, NS, et.bm, wg_counts, grp_off, tile_tab, n_tiles, slot, a_rows,
                             x.st);
         prof_end(x, "dispatch");
         if (e != hipSuccess) return fail(DLM_ERR_HIP, std::string("dispatch: ") + hipGetErrorString(e));
@@ -501,8 +571,8 @@ dlm_status run_layer(Ctx& x, int l) {
         a.a_rows = a_rows;
         a.out = hexp;
         a.ldo = F;
-        a.variant = 11;                                 // ping-pong, third stage for the streamed expert weights (B)
-        TRY(gemm(x, "gemm_expert_gate_up", a, EPI_SWIGLU, true, kExpertBM, kExpertBN, x.w.max_tiles));
+        a.variant = et.variant;
+        TRY(gemm(x, "gemm_expert_gate_up", a, EPI_SWIGLU, true, et.bm, et.bn, max_tiles));
     }
     {
         GemmArgs a = gemm_args(hexp, F, x.wt(L.wd), F, 0, d, F);
@@ -513,8 +583,8 @@ dlm_status run_layer(Ctx& x, int l) {
         a.a_rows = nullptr;
         a.out = y;
         a.ldo = d;
-        a.variant = 11;
-        TRY(gemm(x, "gemm_expert_down", a, EPI_BF16, true, kExpertBM, kExpertBN, x.w.max_tiles));
+        a.variant = et.variant;
+        TRY(gemm(x, "gemm_expert_down", a, EPI_BF16, true, et.bm, et.bn, max_tiles));
     }
     // The combine also normalises each finished row for the next block.
     const bool fuse = l + 1 < c.n_layers;

@@ -73,21 +73,27 @@ __device__ __forceinline__ int swz(int row, int chunk) {
 // QKV projection, computed transposed: rows = q/k/v features, columns =
 // tokens.  A lane then holds, per accumulator, 4 consecutive features of one
 // token (8-byte stores into Q [B][H][S][hd] and K [B][KV][S][hd]; V goes to the
-// transposed layout V^T of kernels.h, consecutive lanes = consecutive keys), and a
-// wave's 128 rows cover whole heads, so the RoPE partners (i, i + hd/2) are in
-// the same lane, accumulator rows i and i + hd/64 (rotate-half, applied in
-// fp32 before rounding).
+// transposed layout V^T of kernels.h, consecutive lanes = consecutive keys).
+// The tile's rows take the features in units of 64 = a 32-feature block of a
+// head's first half followed by its RoPE partners (i + hd/2) from the second
+// half, so that the partners (rotate-half, applied in fp32 before rounding) are
+// in the same lane, accumulators 2u and 2u + 1, and any wave of 64 rows or more
+// holds whole pairs.  The copies into LDS take their rows in this order: it
+// costs nothing, since every lane has its own row offset.
+__device__ __forceinline__ int qkv_unit_feature(int unit, int hd) {     // first feature of a unit
+    return hd == 128 ? (unit >> 1) * 128 + (unit & 1) * 32 : unit * 64;
+}
+__device__ __forceinline__ int qkv_row_feature(int row, int hd) {
+    return qkv_unit_feature(row >> 6, hd) + ((row >> 5) & 1) * (hd >> 1) + (row & 31);
+}
+
 template <int TM, int TN, int HD>
-__device__ __forceinline__ void qkv_epilogue(const GemmArgs& a, const f32x16 (&acc)[TM][TN], int m0, int n0,
-                                             int lrow0, int lcol0) {
-    constexpr int HALF = HD / 2, SPH = HD / 32, POFF = HD / 64;
+__device__ __forceinline__ void qkv_epilogue(const GemmArgs& a, const f32x16 (&acc)[TM][TN], int row0, int n0,
+                                             int lane, int lcol0) {
+    constexpr int HALF = HD / 2;
     const int Hq = a.n_heads * HD, Hk = a.n_kv * HD;
     const int S = a.seq, SK = a.kv_seq;
-    // A wave's 128 rows start on a head boundary, and the Q/K/V boundaries are
-    // head boundaries: the wave is wholly inside Q, K or V (or past M).
-    const int wrow = m0 + (lrow0 & ~127);
-    if (wrow >= a.M) return;
-    const bool rotate = wrow < Hq + Hk;
+    const int half = lane >> 5;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int t_raw = n0 + lcol0 + j * 32;                // token
@@ -95,68 +101,67 @@ __device__ __forceinline__ void qkv_epilogue(const GemmArgs& a, const f32x16 (&a
         const int t = live ? t_raw : a.N - 1;                 // lanes past the end compute, then store nothing
         const int b = t / S, s = t - b * S;
         const int sk = s + a.pos0;                            // position in K / V^T and the RoPE table
-        if (rotate) {
-            // (cos, sin) of the lane's 4 consecutive pairs for each first-half
-            // 32-row block and each group q, all loaded before use.
-            float4 cs[POFF][4][2];
 #pragma unroll
-            for (int ih = 0; ih < POFF; ++ih)
+        for (int u = 0; u < TM / 2; ++u) {
+            // A unit lies inside one head, hence wholly inside Q, K or V (or past M).
+            if (row0 + u * 64 >= a.M) continue;
+            const int f0 = qkv_unit_feature((row0 >> 6) + u, HD);      // first-half features f0 .. f0+31
+            if (f0 < Hq + Hk) {
+                // (cos, sin) of the lane's 4 consecutive pairs of each group q,
+                // all loaded before use.
+                float4 cs[4][2];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int r0 = (lrow0 & 127) + ih * 32 + 8 * q;       // row within the head pair block
-                    const float4* p = reinterpret_cast<const float4*>(a.rope + sk * HALF + (r0 % HALF));
-                    cs[ih][q][0] = p[0];
-                    cs[ih][q][1] = p[1];
+                    const float4* p = reinterpret_cast<const float4*>(a.rope + sk * HALF + f0 % HALF + 8 * q + 4 * half);
+                    cs[q][0] = p[0];
+                    cs[q][1] = p[1];
                 }
-            // Per 32-feature block: the rotated features of this lane's token,
-            // packed, then exchanged between lane halves (swap_halves16) so
-            // that each lane writes 16 consecutive features as two 16-byte
-            // stores.
-            const int half = (lrow0 >> 2) & 1;                  // lane / 32
+                // Per 32-feature block: the rotated features of this lane's
+                // token, packed, then exchanged between lane halves
+                // (swap_halves16) so that each lane writes 16 consecutive
+                // features as two 16-byte stores.
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                uint32_t p[4][2];
+                for (int hi = 0; hi < 2; ++hi) {
+                    uint32_t p[4][2];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int ih = (i % SPH) % POFF;
-                    const float4 c01 = cs[ih][q][0], c23 = cs[ih][q][1];
-                    const float cz[4] = {c01.x, c01.z, c23.x, c23.z};
-                    const float sn[4] = {c01.y, c01.w, c23.y, c23.w};
-                    float v[4];
-                    if ((i % SPH) < POFF) {
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 c01 = cs[q][0], c23 = cs[q][1];
+                        const float cz[4] = {c01.x, c01.z, c23.x, c23.z};
+                        const float sn[4] = {c01.y, c01.w, c23.y, c23.w};
+                        float v[4];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            v[r] = acc[i][j][4 * q + r] * cz[r] - acc[(i + POFF) % TM][j][4 * q + r] * sn[r];
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            v[r] = acc[i][j][4 * q + r] * cz[r] + acc[(i + TM - POFF) % TM][j][4 * q + r] * sn[r];
+                        for (int r = 0; r < 4; ++r) {
+                            const float own = acc[2 * u + hi][j][4 * q + r], other = acc[2 * u + 1 - hi][j][4 * q + r];
+                            // one rounding of the product with sin, then one fma: the
+                            // same bits from every tile shape
+                            v[r] = __fmaf_rn(own, cz[r], __fmul_rn(hi == 0 ? -other : other, sn[r]));
+                        }
+                        p[q][0] = pack_bf16x2(v[0], v[1]);
+                        p[q][1] = pack_bf16x2(v[2], v[3]);
                     }
-                    p[q][0] = pack_bf16x2(v[0], v[1]);
-                    p[q][1] = pack_bf16x2(v[2], v[3]);
+                    swap_halves16(p);
+                    if (live) {
+                        const int fb = f0 + hi * HALF + 16 * half;   // first of this lane's 16 features
+                        const int in_head = fb % HD;
+                        bf16_t* dst = f0 < Hq ? a.q + (((int64_t)b * a.n_heads + fb / HD) * S + s) * HD + in_head
+                                              : a.k + (((int64_t)b * a.n_kv + (fb - Hq) / HD) * SK + sk) * HD + in_head;
+                        *reinterpret_cast<u32x4*>(dst) = u32x4{p[0][0], p[0][1], p[2][0], p[2][1]};
+                        *reinterpret_cast<u32x4*>(dst + 8) = u32x4{p[1][0], p[1][1], p[3][0], p[3][1]};
+                    }
                 }
-                swap_halves16(p);
-                if (live) {
-                    const int fb = m0 + (lrow0 & ~4) + i * 32 + 16 * half;   // first of this lane's 16 features
-                    const int hi0 = fb % HD;
-                    bf16_t* dst = fb < Hq ? a.q + (((int64_t)b * a.n_heads + fb / HD) * S + s) * HD + hi0
-                                          : a.k + (((int64_t)b * a.n_kv + (fb - Hq) / HD) * SK + sk) * HD + hi0;
-                    *reinterpret_cast<u32x4*>(dst) = u32x4{p[0][0], p[0][1], p[2][0], p[2][1]};
-                    *reinterpret_cast<u32x4*>(dst + 8) = u32x4{p[1][0], p[1][1], p[3][0], p[3][1]};
-                }
+            } else if (live) {
+                // V^T: per accumulator 4 rows (features) of one key column
+                const int vs = vt_stride(SK);
+#pragma unroll
+                for (int hi = 0; hi < 2; ++hi)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int fv = f0 + hi * HALF + 8 * q + 4 * half - Hq - Hk;
+                        bf16_t* col = a.v + ((int64_t)(b * a.n_kv + fv / HD) * HD + fv % HD) * vs + vt_pos(sk);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) col[(int64_t)r * vs] = f32_to_bf16(acc[2 * u + hi][j][4 * q + r]);
+                    }
             }
-        } else if (live) {
-            // V^T: per accumulator 4 rows (features) of one key column
-            const int vs = vt_stride(SK);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int fv = m0 + lrow0 + i * 32 + 8 * q - Hq - Hk;
-                    bf16_t* col = a.v + ((int64_t)(b * a.n_kv + fv / HD) * HD + fv % HD) * vs + vt_pos(sk);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) col[(int64_t)r * vs] = f32_to_bf16(acc[i][j][4 * q + r]);
-                }
         }
     }
 }
@@ -237,14 +242,29 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     const bool gather = GROUPED && a.a_rows != nullptr;
     buf_rsrc_t a_rsrc, b_rsrc;
     uint32_t a_off[T::A_INSTR], b_off[T::B_INSTR];
+    // A rows are addressed from this row of A on (a head boundary under EPI_QKV,
+    // whose units reorder the rows inside a head).
+    auto a_first = [&](const TileIdx& t) { return EPI == EPI_QKV ? t.m0 & ~127 : t.row_base + t.m0; };
+    // Byte offset of row tr of the tile, from there.  Rows past the end get bit
+    // 31 set, an offset past the buffer resource's range: the copy then fetches
+    // nothing (it returns zeros), and no result of such a row is stored.
+    auto past_end = [](int row, int rows) -> uint32_t { return (uint32_t)((rows - 1 - row) >> 31) & 0x80000000u; };
+    auto a_row_off = [&](const TileIdx& t, int tr) __attribute__((always_inline)) -> uint32_t {
+        const int r = min(t.m0 + tr, t.rows - 1);
+        int64_t row;
+        if constexpr (EPI == EPI_QKV) row = qkv_row_feature(r, a.head_dim) - (t.m0 & ~127);
+        else row = gather ? (int64_t)a.a_rows[t.row_base + r] : (int64_t)(r - t.m0);
+        return (uint32_t)(row * a.lda * 2) | past_end(t.m0 + tr, t.rows);
+    };
+    auto b_row_off = [&](const TileIdx& t, int tr) __attribute__((always_inline)) -> uint32_t {
+        return (uint32_t)((int64_t)min(tr, a.N - 1 - t.n0) * a.ldb * 2) | past_end(t.n0 + tr, a.N);
+    };
     auto setup_a = [&](const TileIdx& t) {
-        a_rsrc = make_rsrc(gather ? a.A : a.A + (int64_t)(t.row_base + t.m0) * a.lda);
+        a_rsrc = make_rsrc(gather ? a.A : a.A + (int64_t)a_first(t) * a.lda);
 #pragma unroll
         for (int p = 0; p < T::A_INSTR; ++p) {
             const int tr = (wv * T::A_INSTR + p) * RPB + rin;     // row within the tile
-            const int r = min(t.m0 + tr, t.rows - 1);
-            const int64_t grow = gather ? (int64_t)a.a_rows[t.row_base + r] : (int64_t)(r - t.m0);
-            a_off[p] = (uint32_t)(grow * a.lda * 2) + (uint32_t)((pc ^ swz_key<CPR>(tr)) * 16);
+            a_off[p] = a_row_off(t, tr) + (uint32_t)((pc ^ swz_key<CPR>(tr)) * 16);
         }
     };
     auto setup_b = [&](const TileIdx& t) {
@@ -253,8 +273,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
 #pragma unroll
         for (int p = 0; p < T::B_INSTR; ++p) {
             const int tr = (wv * T::B_INSTR + p) * RPB + rin;
-            const int n = min(t.n0 + tr, a.N - 1) - t.n0;
-            b_off[p] = (uint32_t)((int64_t)n * a.ldb * 2) + (uint32_t)((pc ^ swz_key<CPR>(tr)) * 16);
+            b_off[p] = b_row_off(t, tr) + (uint32_t)((pc ^ swz_key<CPR>(tr)) * 16);
         }
     };
     const lds_ptr_t lds = (lds_ptr_t)smem;
@@ -511,11 +530,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
                 }
             }
         } else if constexpr (EPI == EPI_QKV) {
-            static_assert(T::WM % 128 == 0, "a wave's rows must cover whole heads");
+            static_assert(T::WM % 64 == 0, "a wave's rows must be whole units");
             if (a.head_dim == 128)
-                qkv_epilogue<T::TM, T::TN, 128>(a, acc, m0, n0, lrow0, lcol0);
+                qkv_epilogue<T::TM, T::TN, 128>(a, acc, m0 + wm * T::WM, n0, lane, lcol0);
             else
-                qkv_epilogue<T::TM, T::TN, 64>(a, acc, m0, n0, lrow0, lcol0);
+                qkv_epilogue<T::TM, T::TN, 64>(a, acc, m0 + wm * T::WM, n0, lane, lcol0);
         } else if constexpr (EPI == EPI_LMHEAD) {
             // rows = vocabulary ids, cols = tokens.  Per token: (max, first argmax,
             // sum exp(z - max)) over each half tile's BM/2 vocabulary rows.
@@ -641,13 +660,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
                 asm volatile("" : "+v"(ln));
                 const int rin = ln / CPR, pc = ln % CPR;
                 if constexpr (CA) {
-                    rsrc = make_rsrc(gather ? a.A : a.A + (int64_t)(t.row_base + t.m0) * a.lda);
+                    rsrc = make_rsrc(gather ? a.A : a.A + (int64_t)a_first(t) * a.lda);
 #pragma unroll
                     for (int p = 0; p < NI; ++p) {
                         const int tr = (gw * NI + p) * RPB + rin;
-                        const int r = min(t.m0 + tr, t.rows - 1);
-                        const int64_t grow = gather ? (int64_t)a.a_rows[t.row_base + r] : (int64_t)(r - t.m0);
-                        off[p] = (uint32_t)(grow * a.lda * 2) + (uint32_t)((pc ^ swz_key<CPR>(tr)) * 16);
+                        off[p] = a_row_off(t, tr) + (uint32_t)((pc ^ swz_key<CPR>(tr)) * 16);
                     }
                 } else {
                     const bf16_t* Bg = a.B + (GROUPED ? (int64_t)t.g * a.b_group_stride : 0);
@@ -655,8 +672,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
 #pragma unroll
                     for (int p = 0; p < NI; ++p) {
                         const int tr = (gw * NI + p) * RPB + rin;
-                        const int n = min(t.n0 + tr, a.N - 1) - t.n0;
-                        off[p] = (uint32_t)((int64_t)n * a.ldb * 2) + (uint32_t)((pc ^ swz_key<CPR>(tr)) * 16);
+                        off[p] = b_row_off(t, tr) + (uint32_t)((pc ^ swz_key<CPR>(tr)) * 16);
                     }
                 }
             };
@@ -821,7 +837,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
     if (first || !cont) wait_vmcnt<T::N_TOP>();   // K tile 0 landed, later ones may fly
     else wait_vmcnt<T::N_LOOP>();                 // the continuous pipeline's steady-state wait
-    __syncthreads();
+    lds_barrier();                                // (not __syncthreads, whose fence would drain the copies in flight)
     // In grouped mode the last row tile of a group is often partly empty; a
     // wave whose rows all lie past the group's end skips its MFMAs (and
     // fragment reads) but still copies and meets every barrier.
@@ -840,7 +856,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
         for (int kt = 0; kt < nk - 1; ++kt) {
             const int na = sa + 1 == SA ? 0 : sa + 1, nb = sb + 1 == SB ? 0 : sb + 1;
             wait_vmcnt<T::N_LOOP>();                                // own copies of tile kt+1 landed
-            __syncthreads();
+            lds_barrier();
             set_stage(na, nb);
             // Copies of K tiles kt+SA / kt+SB: past the end they belong to the
             // next tile, whose offsets replace this tile's once its last own
@@ -919,7 +935,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     if (flow) {
         // Every wave is done reading K tile nk-1: its stages take the last
         // round of the next tile's first copies (A tile SA-1, B tile SB-1).
-        __syncthreads();
+        lds_barrier();
         issue(SA - 1, (sa0 + nk - 1) % SA, SB - 1, (sb0 + nk - 1) % SB);
         sa0 = (sa0 + nk) % SA;
         sb0 = (sb0 + nk) % SB;
@@ -947,7 +963,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
 
 template <int BM, int BN, int BK, int SA, int SB, int NW, int EPI, bool GROUPED, bool PP>
 hipError_t launch_t(const GemmArgs& a, int max_tiles, hipStream_t st) {
-    if constexpr (EPI == EPI_QKV && (BM / 2) % 128 != 0) {
+    if constexpr (EPI == EPI_QKV && (BM / 2) % 64 != 0) {
         return hipErrorInvalidValue;                       // RoPE pairs must stay inside one wave
     } else {
     auto kernel = gemm_kernel<BM, BN, BK, SA, SB, NW, EPI, GROUPED, PP>;
@@ -982,33 +998,71 @@ hipError_t launch_t(const GemmArgs& a, int max_tiles, hipStream_t st) {
 
 // Tile configurations: BM x BN x BK, SA / SB LDS stages for A / B, NW waves.
 // variant 0: 4 waves; 1: alternative stage/BK choices; 2: 8 waves, 2+2
-// stages; 5: 8 waves with a third B stage (B streamed from far memory, e.g.
-// expert weights); 6: 8 waves with a third A stage (A streamed, e.g. the LM
-// head's vocabulary rows); 11 / 12: as 5 / 6 with the ping-pong schedule (the
-// two waves of a SIMD alternate between multiplying and loading).  The
-// 256x256 8-wave tiles with a third stage use all 160 KB of LDS.
+// stages; 3 / 4: small 4-wave tiles with the stages that keep two (or three)
+// workgroups on a CU, see below; 5: 8 waves with a third B stage (B streamed
+// from far memory, e.g. expert weights); 6: 8 waves with a third A stage (A
+// streamed, e.g. the LM head's vocabulary rows); 11 / 12: as 5 / 6 with the
+// ping-pong schedule (the two waves of a SIMD alternate between multiplying and
+// loading).  The 256x256 8-wave tiles with a third stage use all 160 KB of LDS.
+//
+// Small tiles serve products with too few 256x256 tiles for 256 CUs (one to a
+// few thousand rows).  What bounds them is the latency of a K step (copy,
+// barrier, fragment reads), so a step in flight more and a second workgroup
+// per CU count for more than reuse: the O projection of 512 rows (512 x 2048 x
+// 2048) takes 29 us on 128x64 tiles with two stages, 13.5 with three less, 11
+// on 64x64 tiles with five.
 template <int EPI, bool GROUPED>
-hipError_t launch_tiles(const GemmArgs& a, int bm, int bn, int max_tiles, hipStream_t st) {
+hipError_t launch_small(const GemmArgs& a, int bm, int bn, int max_tiles, hipStream_t st) {
+    if (a.variant == 3) {
+        if constexpr (EPI == EPI_RESID || EPI == EPI_F32)
+            if (bm == 64 && bn == 64) return launch_t<64, 64, 64, 5, 5, 4, EPI, GROUPED, false>(a, max_tiles, st);
+        if constexpr (EPI == EPI_SWIGLU || EPI == EPI_BF16 || EPI == EPI_F32)
+            if (bm == 64 && bn == 128) return launch_t<64, 128, 64, 3, 3, 4, EPI, GROUPED, false>(a, max_tiles, st);
+        if constexpr (EPI == EPI_QKV || EPI == EPI_F32)
+            if (bm == 128 && bn == 64) return launch_t<128, 64, 64, 3, 3, 4, EPI, GROUPED, false>(a, max_tiles, st);
+        if constexpr (EPI != EPI_QKV)
+            if (bm == 128 && bn == 128) return launch_t<128, 128, 64, 2, 3, 4, EPI, GROUPED, false>(a, max_tiles, st);
+    }
+    if (a.variant == 4) {
+        if constexpr (EPI == EPI_RESID || EPI == EPI_F32)
+            if (bm == 64 && bn == 64) return launch_t<64, 64, 64, 3, 3, 4, EPI, GROUPED, false>(a, max_tiles, st);
+        if constexpr (EPI == EPI_QKV || EPI == EPI_F32)
+            if (bm == 128 && bn == 128) return launch_t<128, 128, 64, 3, 2, 4, EPI, GROUPED, false>(a, max_tiles, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+// The products of the pass: small tiles and the ping-pong tile.
+template <int EPI, bool GROUPED>
+hipError_t launch_pass(const GemmArgs& a, int bm, int bn, int max_tiles, hipStream_t st) {
+    if (bm == 256 && bn == 256 && a.variant == 11)
+        return launch_t<256, 256, 64, 2, 3, 8, EPI, GROUPED, true>(a, max_tiles, st);
+    return launch_small<EPI, GROUPED>(a, bm, bn, max_tiles, st);
+}
+
+// The plain fp32 product: every configuration.
+hipError_t launch_f32(const GemmArgs& a, int bm, int bn, hipStream_t st) {
     if (a.variant == 1) {
-        if (bm == 256 && bn == 256) return launch_t<256, 256, 32, 4, 4, 4, EPI, GROUPED, false>(a, max_tiles, st);
-        if (bm == 128 && bn == 128) return launch_t<128, 128, 64, 3, 3, 4, EPI, GROUPED, false>(a, max_tiles, st);
-        if (bm == 256 && bn == 128) return launch_t<256, 128, 64, 2, 2, 4, EPI, GROUPED, false>(a, max_tiles, st);
+        if (bm == 256 && bn == 256) return launch_t<256, 256, 32, 4, 4, 4, EPI_F32, false, false>(a, 0, st);
+        if (bm == 128 && bn == 128) return launch_t<128, 128, 64, 3, 3, 4, EPI_F32, false, false>(a, 0, st);
+        if (bm == 256 && bn == 128) return launch_t<256, 128, 64, 2, 2, 4, EPI_F32, false, false>(a, 0, st);
         return hipErrorInvalidValue;
     }
     if (bm == 256 && bn == 256) {
-        if (a.variant == 2) return launch_t<256, 256, 64, 2, 2, 8, EPI, GROUPED, false>(a, max_tiles, st);
-        if (a.variant == 5) return launch_t<256, 256, 64, 2, 3, 8, EPI, GROUPED, false>(a, max_tiles, st);
-        if (a.variant == 6) return launch_t<256, 256, 64, 3, 2, 8, EPI, GROUPED, false>(a, max_tiles, st);
-        if (a.variant == 11) return launch_t<256, 256, 64, 2, 3, 8, EPI, GROUPED, true>(a, max_tiles, st);
-        if (a.variant == 12) return launch_t<256, 256, 64, 3, 2, 8, EPI, GROUPED, true>(a, max_tiles, st);
+        if (a.variant == 2) return launch_t<256, 256, 64, 2, 2, 8, EPI_F32, false, false>(a, 0, st);
+        if (a.variant == 5) return launch_t<256, 256, 64, 2, 3, 8, EPI_F32, false, false>(a, 0, st);
+        if (a.variant == 6) return launch_t<256, 256, 64, 3, 2, 8, EPI_F32, false, false>(a, 0, st);
+        if (a.variant == 12) return launch_t<256, 256, 64, 3, 2, 8, EPI_F32, false, true>(a, 0, st);
     }
-    if (a.variant != 0) return hipErrorInvalidValue;
-    if (bm == 256 && bn == 256) return launch_t<256, 256, 64, 2, 2, 4, EPI, GROUPED, false>(a, max_tiles, st);
-    if (bm == 256 && bn == 128) return launch_t<256, 128, 64, 3, 3, 4, EPI, GROUPED, false>(a, max_tiles, st);
-    if (bm == 128 && bn == 256) return launch_t<128, 256, 64, 3, 3, 4, EPI, GROUPED, false>(a, max_tiles, st);
-    if (bm == 128 && bn == 128) return launch_t<128, 128, 64, 2, 2, 4, EPI, GROUPED, false>(a, max_tiles, st);
-    if (bm == 128 && bn == 64) return launch_t<128, 64, 64, 2, 2, 4, EPI, GROUPED, false>(a, max_tiles, st);
-    return hipErrorInvalidValue;
+    if (a.variant == 0) {
+        if (bm == 256 && bn == 256) return launch_t<256, 256, 64, 2, 2, 4, EPI_F32, false, false>(a, 0, st);
+        if (bm == 256 && bn == 128) return launch_t<256, 128, 64, 3, 3, 4, EPI_F32, false, false>(a, 0, st);
+        if (bm == 128 && bn == 256) return launch_t<128, 256, 64, 3, 3, 4, EPI_F32, false, false>(a, 0, st);
+        if (bm == 128 && bn == 128) return launch_t<128, 128, 64, 2, 2, 4, EPI_F32, false, false>(a, 0, st);
+        if (bm == 128 && bn == 64) return launch_t<128, 64, 64, 2, 2, 4, EPI_F32, false, false>(a, 0, st);
+        return hipErrorInvalidValue;
+    }
+    return launch_pass<EPI_F32, false>(a, bm, bn, 0, st);
 }
 
 }  // namespace
@@ -1018,21 +1072,22 @@ hipError_t launch_gemm(const GemmArgs& a, int epi, bool grouped, int bm, int bn,
     if (a.K % 64 != 0 || a.N <= 0 || (!grouped && a.M <= 0)) return hipErrorInvalidValue;
     switch (epi) {
         case EPI_BF16:
-            return grouped ? launch_tiles<EPI_BF16, true>(a, bm, bn, max_tiles, st)
-                           : launch_tiles<EPI_BF16, false>(a, bm, bn, max_tiles, st);
+            return grouped ? launch_pass<EPI_BF16, true>(a, bm, bn, max_tiles, st) : hipErrorInvalidValue;
         case EPI_SWIGLU:
-            return grouped ? launch_tiles<EPI_SWIGLU, true>(a, bm, bn, max_tiles, st)
-                           : launch_tiles<EPI_SWIGLU, false>(a, bm, bn, max_tiles, st);
+            return grouped ? launch_pass<EPI_SWIGLU, true>(a, bm, bn, max_tiles, st)
+                           : launch_pass<EPI_SWIGLU, false>(a, bm, bn, max_tiles, st);
         case EPI_F32:
-            return grouped ? hipErrorInvalidValue : launch_tiles<EPI_F32, false>(a, bm, bn, max_tiles, st);
+            return grouped ? hipErrorInvalidValue : launch_f32(a, bm, bn, st);
         case EPI_RESID:
-            return grouped ? hipErrorInvalidValue : launch_tiles<EPI_RESID, false>(a, bm, bn, max_tiles, st);
+            return grouped ? hipErrorInvalidValue : launch_pass<EPI_RESID, false>(a, bm, bn, max_tiles, st);
         case EPI_QKV:
-            return grouped ? hipErrorInvalidValue : launch_tiles<EPI_QKV, false>(a, bm, bn, max_tiles, st);
+            return grouped ? hipErrorInvalidValue : launch_pass<EPI_QKV, false>(a, bm, bn, max_tiles, st);
         case EPI_LMHEAD:
-            return grouped ? hipErrorInvalidValue : launch_tiles<EPI_LMHEAD, false>(a, bm, bn, max_tiles, st);
+            if (grouped || bm != 256 || bn != 256 || a.variant != 12) return hipErrorInvalidValue;
+            return launch_t<256, 256, 64, 3, 2, 8, EPI_LMHEAD, false, true>(a, 0, st);
         case EPI_F32_T:
-            return grouped ? hipErrorInvalidValue : launch_tiles<EPI_F32_T, false>(a, bm, bn, max_tiles, st);
+            if (grouped || bm != 256 || bn != 256 || a.variant != 0) return hipErrorInvalidValue;
+            return launch_t<256, 256, 64, 2, 2, 4, EPI_F32_T, false, false>(a, 0, st);
         default:
             return hipErrorInvalidValue;
     }

@@ -34,6 +34,19 @@ pytestmark = pytest.mark.gpu
     (8229, 2100, 128, ((11 << 16) | 256, 256)),
     (8229, 2100, 320, ((11 << 16) | 256, 256)),
     (8229, 2100, 320, ((12 << 16) | 256, 256)),
+    # small 4-wave tiles: one row, ragged edges, fewer K tiles than stages,
+    # several output tiles per workgroup with copies running on across them
+    (1, 1, 64, ((3 << 16) | 64, 64)),
+    (65, 63, 256, ((3 << 16) | 64, 64)),
+    (3001, 2100, 448, ((3 << 16) | 64, 64)),
+    (3001, 2100, 320, ((4 << 16) | 64, 64)),
+    (65, 129, 128, ((3 << 16) | 64, 128)),
+    (2900, 4100, 320, ((3 << 16) | 64, 128)),
+    (129, 65, 192, ((3 << 16) | 128, 64)),
+    (4100, 2900, 320, ((3 << 16) | 128, 64)),
+    (130, 255, 64, ((3 << 16) | 128, 128)),
+    (4100, 3900, 256, ((3 << 16) | 128, 128)),
+    (4100, 3900, 256, ((4 << 16) | 128, 128)),
 ])
 def test_gemm_matches_fp32_reference(m, n, k, tile):
     need_gpu()

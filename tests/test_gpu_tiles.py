@@ -1,0 +1,48 @@
+"""A row's result does not depend on how many rows share the call: products take
+their tiles by the number of rows, and every tile adds in the same order, so a
+sequence alone and the same sequence in larger batches give the same bits."""
+
+from __future__ import annotations
+
+import pytest
+
+from tests.gpu_util import log, need_gpu
+
+pytestmark = pytest.mark.gpu
+
+BASE = dict(n_layers=1, rope_theta=10000.0, norm_eps=1e-6, init_std=0.05, lm_head_scale=1.0, vocab=300, mask_id=299)
+DENSE = dict(BASE, n_experts=0, top_k=0, expert_ffn_dim=0, n_shared_experts=0)
+
+SHAPES = {
+    # d_model below and at the length from which 256x256 tiles are taken, head
+    # widths 64 and 128 (the order of the QKV rows), dense and expert FFNs
+    "dense_hd64": dict(DENSE, d_model=256, n_heads=4, n_kv_heads=2, head_dim=64, ffn_dim=320),
+    "dense_hd128_wide": dict(DENSE, d_model=2048, n_heads=16, n_kv_heads=2, head_dim=128, ffn_dim=2112),
+    "moe_hd128": dict(BASE, d_model=256, n_heads=2, n_kv_heads=1, head_dim=128, ffn_dim=0, n_experts=24, top_k=3,
+                      expert_ffn_dim=192, n_shared_experts=1),
+    "moe_hd64_no_shared": dict(BASE, d_model=384, n_heads=6, n_kv_heads=2, head_dim=64, ffn_dim=0, n_experts=5,
+                               top_k=1, expert_ffn_dim=64, n_shared_experts=0),
+}
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+@pytest.mark.parametrize("seq", [1, 37, 130])
+def test_rows_do_not_depend_on_the_batch(name, seq):
+    need_gpu()
+    import torch
+    from paper_2608_02625_amd import Refiner
+    shape = SHAPES[name]
+    r = Refiner(shape, 7)
+    d = shape["d_model"]
+    top = max(2, (9000 if d < 1024 else 4500) // seq)
+    g = torch.Generator().manual_seed(seq)
+    x = torch.randn(top * seq, d, generator=g).cuda()
+    ref = r.debug_layer(0, x[:seq].clone(), 1, seq)
+    assert torch.isfinite(ref).all()
+    batches = sorted({b for b in (2, 3, 300 // seq, 700 // seq, 1500 // seq, 2600 // seq, 4400 // seq, top) if 1 < b <= top})
+    for b in batches:
+        y = r.debug_layer(0, x[:b * seq].clone(), b, seq)
+        assert torch.equal(y[:seq], ref), f"batch {b}"
+        lone = r.debug_layer(0, x[(b - 1) * seq:b * seq].clone(), 1, seq)
+        assert torch.equal(y[-seq:], lone), f"last row of batch {b}"
+    log(f"[tiles {name} seq {seq}] batches {batches} equal the sequence alone")
