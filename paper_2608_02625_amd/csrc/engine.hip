@@ -241,7 +241,7 @@ Workspace plan_workspace(const dlm_config& c, int B, int P, int D) {
         w.n_tiles = add(4);
         w.slot = add(T * k * 4);
         w.a_rows = add((int64_t)w.rows_total * 4);
-        w.ecount = add((T + 31) / 32 * E * 4);           // per router workgroup and expert counts
+        w.ecount = add((T + 31) / 32 * E * 4);           // per expert and router group (of 32 tokens) counts
         w.hexp = add((int64_t)w.rows_total * c.expert_ffn_dim * 2);
         w.y = add((int64_t)w.rows_total * d * 2);
     }
@@ -551,13 +551,33 @@ dlm_status run_layer(Ctx& x, int l) {
     bf16_t* hexp = x.at<bf16_t>(x.w.hexp);
     bf16_t* y = x.at<bf16_t>(x.w.y);
     {
+        // The partial logits go where the expert products will write (nothing
+        // there is live yet), or, where a logit row is longer than an expert
+        // row pair, into Q, K, V^T and the attention output: 256 bytes or more
+        // each per token, a row of 256 logits.
+        const int64_t cap_y = (int64_t)(x.w.y - x.w.hexp) + (int64_t)rows_total * d * 2;
+        const bool in_y = cap_y >= (int64_t)Tf * E * 4;
+        float* parts = x.at<float>(in_y ? x.w.hexp : x.w.q);
+        const int n_split = router_splits(Tf, d, E, in_y ? cap_y : (int64_t)Tf * E * 4);
+        // Selection counts of groups of 8 tokens (see router_group_tokens) lie
+        // behind the tile table where that buffer holds both; else groups of
+        // 32, whose counts have a place of their own.
+        const size_t tab_bytes = align_up((size_t)max_tiles * 8);
+        int group = router_group_tokens(Tf, E, 8);
+        if (in_y && tab_bytes + (size_t)E * ((Tf + group - 1) / group) * 4 <= (size_t)Tf * H * hd * 2)
+            wg_counts = x.at<int32_t>(x.w.attn + tab_bytes);
+        else
+            group = router_group_tokens(Tf, E, 32);
+        prof_begin(x, "router_logits");
+        hipError_t e = launch_router_logits(h, x.wt(L.wr), Tf, d, E, n_split, parts, x.st);
+        prof_end(x, "router_logits");
+        if (e != hipSuccess) return fail(DLM_ERR_HIP, std::string("router_logits: ") + hipGetErrorString(e));
         prof_begin(x, "router_topk");
-        hipError_t e = launch_router_topk(h, x.wt(L.wr), Tf, d, E, kk, ids, wts, slot, wg_counts, x.st,
-                                          x.dbg_router_logits);
+        e = launch_router_topk(parts, n_split, Tf, E, kk, group, ids, wts, slot, wg_counts, x.st, x.dbg_router_logits);
         prof_end(x, "router_topk");
         if (e != hipSuccess) return fail(DLM_ERR_HIP, std::string("router_topk: ") + hipGetErrorString(e));
         prof_begin(x, "dispatch");
-        e = launch_dispatch(ids, Tf, kk, E, NS, et.bm, wg_counts, grp_off, tile_tab, n_tiles, slot, a_rows,
+        e = launch_dispatch(ids, Tf, kk, E, NS, group, et.bm, wg_counts, grp_off, tile_tab, n_tiles, slot, a_rows,
                             x.st);
         prof_end(x, "dispatch");
         if (e != hipSuccess) return fail(DLM_ERR_HIP, std::string("dispatch: ") + hipGetErrorString(e));

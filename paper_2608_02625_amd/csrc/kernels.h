@@ -140,20 +140,29 @@ hipError_t launch_draft_select(int32_t* tokens, int B, int S, int c0, int L, con
 void launch_vt_pad_zero(bf16_t* vt, int64_t rows, int S, hipStream_t st);
 
 // ----------------------------------------------------------------- moe.hip
-// Router logits of T tokens (h [T][d] bf16, Wr [E][d] bf16, E <= 256), softmax
-// top-k (k <= 8; ties -> lower id) with renormalised weights.  Tokens are
-// handled 32 per router workgroup: pos[t][j] = rank of the selection among its
-// workgroup's selections of expert ids[t][j]; wg_counts[E][ceil(T/32)] = per
-// expert and workgroup selection counts.  logits (may be null): the router
-// logits float [T][E] (test hook).
-hipError_t launch_router_topk(const bf16_t* h, const bf16_t* Wr, int T, int d, int E, int k, int32_t* ids,
+// Router logits of T tokens (h [T][d] bf16, Wr [E][d] bf16, E <= 256), as n_split
+// partial sums parts [n_split][T][E] (1, 2, 4 or 8, at most router_parts(d));
+// their tree sum has the same bits for every n_split.  router_splits: the
+// number to use where `capacity` bytes are free for the parts.
+int router_parts(int d);
+int router_splits(int T, int d, int E, int64_t capacity);
+hipError_t launch_router_logits(const bf16_t* h, const bf16_t* Wr, int T, int d, int E, int n_split, float* parts,
+                                hipStream_t st);
+// Softmax top-k (k <= 8; ties -> lower id) of those logits with renormalised
+// weights.  Tokens are handled in groups, one workgroup each: pos[t][j] = rank
+// of the selection among its workgroup's selections of expert ids[t][j];
+// wg_counts[E][ceil(T / group_tokens)] = per expert and workgroup selection
+// counts.  logits (may be null): the router logits float [T][E] (test hook).
+// router_group_tokens: group size to use, a multiple of `least`.
+int router_group_tokens(int T, int E, int least);
+hipError_t launch_router_topk(const float* parts, int n_split, int T, int E, int k, int group_tokens, int32_t* ids,
                               float* w, int32_t* pos, int32_t* wg_counts, hipStream_t st, float* logits = nullptr);
 // Group row ranges (E routed + n_shared groups of T rows), tile table of the
 // grouped GEMM (tile height bm), slot[t][j] (from pos, in place) and
-// a_rows[row] = token.  wg_counts is turned into per-workgroup offsets.
-hipError_t launch_dispatch(const int32_t* ids, int T, int k, int E, int n_shared, int bm, int32_t* wg_counts,
-                           int32_t* grp_off, int2* tile_tab, int32_t* n_tiles, int32_t* slot, int32_t* a_rows,
-                           hipStream_t st);
+// a_rows[row] = token.
+hipError_t launch_dispatch(const int32_t* ids, int T, int k, int E, int n_shared, int group_tokens, int bm,
+                           const int32_t* wg_counts, int32_t* grp_off, int2* tile_tab, int32_t* n_tiles,
+                           int32_t* slot, int32_t* a_rows, hipStream_t st);
 // x[t] += sum_j w[t][j] * Y[slot[t][j]] + sum_s Y[shared rows]
 // With g_next != nullptr, also writes h_next = RMSNorm(x) * g_next (bf16) for
 // the next block (the combine holds each finished residual row).

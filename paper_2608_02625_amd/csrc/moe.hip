@@ -8,207 +8,228 @@
 
 namespace {
 
-// XOR key of the 16-byte chunks of an LDS row of CPR chunks (8, 16 or 32):
-// a fragment read of 32 consecutive rows at one logical chunk hits distinct
-// banks (with 16 or more chunks per row the low four row bits suffice).
-template <int CPR>
-__device__ __forceinline__ int rkey(int row) {
-    if constexpr (CPR >= 16) return row & 15;
-    else return (row & 7) ^ ((row >> 3) & 1);
-}
+// XOR key of the 16-byte chunks of a 128-byte LDS row: a fragment read of 32
+// consecutive rows at one logical chunk hits distinct banks.
+__device__ __forceinline__ int rkey(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
-// Router + top-k for 32 tokens per workgroup (8 waves).
-// z^T[e][t] = sum_c Wr[e][c] h[t][c] on v_mfma_f32_32x32x16_bf16 with experts
-// as rows (NB <= 8 blocks of 32) and tokens as columns.  K advances ROWB / 2
-// columns at a time (64, 128 or 256) through 3 to 8 LDS stages that the
-// waves fill with buffer loads straight from global memory (whole ROWB-byte
-// row segments, 16-byte chunks XOR-swizzled), so every byte of h and Wr is
-// fetched once per workgroup in full cache lines.  Each expert block's
-// 16-wide K steps are dealt round-robin to 8 / NB waves and the parts are
-// added in a fixed order.
-// Each wave then selects for 4 tokens; lane r < k records selection r with its
-// rank among this workgroup's selections of the same expert (LDS counter), and
-// the workgroup's per-expert counts go to wg_counts[E][workgroup].  Ranks only
-// order rows inside an expert's group.
-template <int NB, int ROWB>
-__global__ __launch_bounds__(512) void router_topk_kernel(const bf16_t* __restrict__ h, const bf16_t* __restrict__ Wr,
-                                                         int T, int d, int E, int k, int32_t* __restrict__ ids,
-                                                         float* __restrict__ wts, int32_t* __restrict__ pos,
-                                                         int32_t* __restrict__ wg_counts, float* __restrict__ logits) {
-    constexpr int NW = 8;                            // waves
-    static_assert(NB >= 1 && NB <= NW, "expert blocks");
-    constexpr int KSPLIT = NW / NB;                  // waves sharing an expert block
-    constexpr int EP = NB * 32;                      // padded expert count (LDS row)
-    constexpr int ZROW = EP + 4;                     // row stride: 16-byte aligned, 4 banks of skew
-    constexpr int CPR = ROWB / 16;                   // 16-byte chunks per LDS row
-    constexpr int RPB = 1024 / ROWB;                 // rows per 1 KB copy block
-    constexpr int HB = 32 / RPB;                     // copy blocks of token rows
-    constexpr int KSTEPS = ROWB / 32;                // 16-wide K steps per chunk
-    constexpr int H_BYTES = 32 * ROWB, STAGE = H_BYTES + EP * ROWB;
-    // Stages: as many as fit in 150 KB (3 to 8), so that several K chunks
-    // are in flight while one is multiplied (the K loop is latency-bound).
-    constexpr int NS = 150 * 1024 / STAGE < 3 ? 3 : (150 * 1024 / STAGE > 8 ? 8 : 150 * 1024 / STAGE);
-    constexpr int NBLK = STAGE / 1024;               // 1 KB copy blocks per stage (RPB rows each)
-    constexpr int NI = (NBLK + NW - 1) / NW;         // copies per wave and stage (the last block repeats)
-    constexpr int ZBYTES = KSPLIT * 32 * ZROW * 4 + 32 * EP * 8;
-    constexpr int LBYTES = NS * STAGE > ZBYTES ? NS * STAGE : ZBYTES;
-    __shared__ __attribute__((aligned(16))) char smem[LBYTES];   // K stages, then logit parts and keys
-    __shared__ int lcnt[EP];
-    typedef float zrow_t[32][ZROW];
-    zrow_t* zs = reinterpret_cast<zrow_t*>(smem);
-    uint64_t* keys = reinterpret_cast<uint64_t*>(smem + KSPLIT * 32 * ZROW * 4);   // [32][EP]
-
-    // The wave index is made scalar so that branches on it are real
-    // branches: an MFMA under an EXEC mask still accumulates.
+// Router logits z[t][e] = sum_c h[t][c] Wr[e][c], 64 tokens x 64 experts per
+// workgroup (4 waves of 32x32) on v_mfma_f32_32x32x16_bf16.  K is cut into
+// n_parts (2, 4 or 8) equal parts whose sums are added as a balanced tree,
+// ((p0 + p1) + (p2 + p3)) + ..., so that the result has the same bits however
+// the parts are spread over workgroups: blockIdx.z = s adds parts
+// s * CH .. s * CH + CH - 1 and writes its subtree to out[s][T][E]; the top-k
+// kernel adds the subtrees.
+// A few hundred tokens would leave this to a handful of workgroups, each
+// streaming all of Wr and walking d in one chain; with the parts on workgroups
+// of their own the chain is n_parts times shorter.  Copies go global -> LDS (3
+// stages of 64 columns), 48 KB, three workgroups per CU.
+template <int CH>
+__global__ __launch_bounds__(256) void router_logits_kernel(const bf16_t* __restrict__ h, const bf16_t* __restrict__ Wr,
+                                                            int T, int d, int E, int part, float* __restrict__ out) {
+    constexpr int NS = 3, BK = 64, ROW = BK * 2, HALF = 64 * ROW, STAGE = 2 * HALF;
+    constexpr int NI = STAGE / 1024 / 4;             // 1 KB copies (8 rows) per wave and stage
+    __shared__ __attribute__((aligned(16))) char smem[NS * STAGE];
     const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
     const int g = lane >> 5, j = lane & 31;
-    const int t0 = blockIdx.x * 32;
-    const int blk0 = wave / KSPLIT, kc = wave % KSPLIT;
-    for (int e = threadIdx.x; e < EP; e += NW * 64) lcnt[e] = 0;
+    const int t0 = blockIdx.x * 64, e0 = blockIdx.y * 64;
+    const int k0 = blockIdx.z * CH * part;           // first column
+    const int wt = wave >> 1, we = wave & 1;
 
-    // Copy block q of a stage: q < HB holds token rows RPB q .. RPB q + RPB - 1
-    // of h, the others expert rows of Wr (rows past T or E repeat the last one).
-    const buf_rsrc_t h_rsrc = make_rsrc(h), w_rsrc = make_rsrc(Wr);
+    // Rows past T or E lie past the buffers' ranges: nothing is fetched for them.
+    const buf_rsrc_t h_rsrc = make_rsrc(h + (int64_t)t0 * d, (int)min((int64_t)(T - t0) * d * 2, (int64_t)0x7fffffff));
+    const buf_rsrc_t w_rsrc = make_rsrc(Wr + (int64_t)e0 * d, (E - e0) * d * 2);
     uint32_t off[NI];
-    bool is_h[NI];
-    int dst[NI];
 #pragma unroll
     for (int p = 0; p < NI; ++p) {
-        const int q = min(wave * NI + p, NBLK - 1);
-        const int rr = lane / CPR, pc = lane % CPR;
-        is_h[p] = q < HB;
-        const int row = is_h[p] ? q * RPB + rr : (q - HB) * RPB + rr;
-        const int64_t grow = is_h[p] ? min(t0 + row, T - 1) : min(row, E - 1);
-        off[p] = (uint32_t)(grow * d * 2) + (uint32_t)((pc ^ rkey<CPR>(row)) * 16);
-        dst[p] = q * 1024;
+        const int row = ((wave & 1) * NI + p) * 8 + lane / 8;     // waves 0, 1 copy token rows, 2, 3 expert rows
+        off[p] = (uint32_t)(row * d * 2) + (uint32_t)(((lane % 8) ^ rkey(row)) * 16);
     }
     const lds_ptr_t lds = (lds_ptr_t)smem;
     typedef __attribute__((address_space(3))) char lds_char;
     typedef __attribute__((address_space(3))) const bf16x8 lds_frag;
-    auto issue = [&](int c, int stage) {             // K chunk c (ROWB / 2 columns) into a stage
+    const int nk = CH * part / BK;
+    auto issue = [&](int kt, int stage) {
+        const int dst = stage * STAGE + wave * NI * 1024;
 #pragma unroll
         for (int p = 0; p < NI; ++p)
-            lds_dma16_buf(is_h[p] ? h_rsrc : w_rsrc, off[p], c * ROWB, (lds_ptr_t)((lds_char*)lds + stage * STAGE + dst[p]));
+            lds_dma16_buf(wave < 2 ? h_rsrc : w_rsrc, off[p], (k0 + kt * BK) * 2, (lds_ptr_t)((lds_char*)lds + dst + p * 1024));
     };
-
-    f32x16 acc;
+    f32x16 acc, tree[3];
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    const int nk = d / (ROWB / 2);
-    const int hfrag = j * ROWB, wfrag = H_BYTES + (blk0 * 32 + j) * ROWB, key = rkey<CPR>(j);
 #pragma unroll
-    for (int s = 0; s < NS; ++s) issue(min(s, nk - 1), s);
-    for (int c = 0; c < nk; ++c) {
-        // own copies of K chunk c landed (later chunks may fly), then
-        // everyone's; the stage of chunk c-1 is free for chunk c+NS-1
-        if (c == 0) wait_vmcnt<NI * (NS - 1)>();
-        else wait_vmcnt<NI * (NS - 2)>();
-        __syncthreads();
-        if (c > 0) issue(min(c + NS - 1, nk - 1), (c + NS - 1) % NS);
-        const int sb = (c % NS) * STAGE;
+    for (int l = 0; l < 3; ++l) tree[l] = acc;
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            if ((c * KSTEPS + ks) % KSPLIT != kc) continue;   // wave-uniform
-            const int co = ((2 * ks + g) ^ key) << 4;
-            const bf16x8 wf = *(lds_frag*)((lds_char*)lds + sb + wfrag + co);
-            const bf16x8 hf = *(lds_frag*)((lds_char*)lds + sb + hfrag + co);
-            acc = mfma32x32x16(wf, hf, acc);
+    for (int s = 0; s < NS - 1; ++s) issue(min(s, nk - 1), s);
+    const int ha = (wt * 32 + j) * ROW, wa = HALF + (we * 32 + j) * ROW, key = rkey(j);
+    const int per = part / BK;                       // K tiles per part
+    int stage = 0, kt = 0;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        for (int q = 0; q < per; ++q, ++kt) {
+            wait_vmcnt<NI * (NS - 2)>();             // own copies of K tile kt landed
+            lds_barrier();                           // everyone's; the stage of K tile kt - 1 is free
+            issue(min(kt + NS - 1, nk - 1), (stage + NS - 1) % NS);
+            const int sb = stage * STAGE;
+            stage = (stage + 1) % NS;
+#pragma unroll
+            for (int ks = 0; ks < BK / 16; ++ks) {
+                const int co = ((2 * ks + g) ^ key) << 4;
+                const bf16x8 hf = *(lds_frag*)((lds_char*)lds + sb + ha + co);
+                const bf16x8 wf = *(lds_frag*)((lds_char*)lds + sb + wa + co);
+                acc = mfma32x32x16(hf, wf, acc);
+            }
         }
-    }
-    wait_all_memory();                               // no copy may land in the logit parts
-    __syncthreads();
-    // acc[e]: expert blk0*32 + 8*(e/4) + 4*g + e%4, token j
+        // part c done: add the subtrees that end with it
+        f32x16 v = acc;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) zs[kc][j][blk0 * 32 + 8 * (e >> 2) + 4 * g + (e & 3)] = acc[e];
-    __syncthreads();
-    // Sum the K parts in a fixed order; logits of experts >= E become -inf,
-    // and so does a NaN logit, so that the order below stays total and every
-    // token receives exactly k distinct experts whatever its input.  Each
-    // (token, expert) also gets a 64-bit key: the logit's bits made orderable
-    // as an unsigned integer above the complement of the expert id, so that
-    // "larger logit, or equal logit and lower id" is one unsigned compare.
-    for (int i = threadIdx.x; i < 32 * EP; i += NW * 64) {
-        const int tt = i / EP, e = i - tt * EP;
-        float z = zs[0][tt][e];
+        for (int l = 0; l < 3; ++l) {
+            if (((c >> l) & 1) == 0) {
+                tree[l] = v;
+                break;
+            }
 #pragma unroll
-        for (int s = 1; s < KSPLIT; ++s) z += zs[s][tt][e];
-        if (logits && e < E && t0 + tt < T) logits[(int64_t)(t0 + tt) * E + e] = z;   // test hook
-        z = (e < E && z == z) ? z + 0.f : -INFINITY;         // (+0.f: -0 and +0 compare equal)
-        zs[0][tt][e] = z;
-        const uint32_t u = __float_as_uint(z);
-        const uint32_t ord = u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
-        keys[tt * EP + e] = ((uint64_t)ord << 32) | (uint32_t)~e;
+            for (int e = 0; e < 16; ++e) v[e] += tree[l][e];
+        }
+        if (c == CH - 1) {
+            // v[e]: token 8*(e/4) + 4*g + e%4 of the wave's 32, expert j
+            const int ex = e0 + we * 32 + j;
+            float* o = out + (int64_t)blockIdx.z * T * E;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int t = t0 + wt * 32 + 8 * (e >> 2) + 4 * g + (e & 3);
+                if (t < T && ex < E) o[(int64_t)t * E + ex] = v[e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
     }
-    __syncthreads();
+    wait_all_memory();                               // no copy may still land in LDS when the workgroup ends
+}
 
-    // Top-k per token, four tokens per wave; lane owns experts
-    // lane + 64q.  p = softmax(z) over the E experts; expert e is selection
-    // r = #{e' : key[e'] > key[e]} if r < k (the k largest logits, ties ->
-    // lower id, in descending order); the selected probabilities are
-    // renormalised to sum to one.
-    constexpr int NQ = (EP + 63) / 64;
-    constexpr int TPW = 32 / NW;                     // tokens per wave
-    // Ranks of all of the wave's tokens in one pass over the keys (their LDS
-    // broadcast reads overlap).
-    uint64_t kq[TPW][NQ];
-    int rank[TPW][NQ];
-#pragma unroll
-    for (int i = 0; i < TPW; ++i)
+// Largest of the wave's 64 unsigned values, on DPP lane moves.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    auto step = [&](uint32_t o) { v = o > v ? o : v; };
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));   // row_half_mirror
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xF, 0xF, false));   // row_mirror
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xA, 0xF, false));   // row_bcast:15 into rows 1, 3
+    step((uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xC, 0xF, false));   // row_bcast:31 into rows 2, 3
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+#else
+    return v;
+#endif
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+#else
+    return v;
+#endif
+}
+
+// Softmax top-k of group_tokens tokens per workgroup (8 waves, one token per
+// wave at a time; lane l owns experts l + 64q, E <= 64 NQ).  The logits are the
+// tree sum of n_split subtrees.  A NaN logit counts as -inf, so that the order
+// is total and every token receives exactly k distinct experts whatever its
+// input.  Selections are taken one by one, the largest logit with ties to the
+// lower id: the maximum of order-preserving keys over the wave, then the first
+// owner of that key (a ballot per expert block): k maxima of about 25
+// instructions each, where ranking every expert takes E compares per expert
+// owned.  Bound by those instructions.  Logits + top-k + dispatch against one
+// kernel of 32 tokens per workgroup that did both, us with each launch (4.4):
+// 10240 tokens, 256 experts, d 4096: 60 + 42 + 12 against 228 + 100; 640
+// tokens, 64 experts, d 2048: 6.5 + 6.4 + 7.2 against 21.5 + 7.2; 32768 tokens:
+// 40 + 31 + 13 against 84 + 114.
+// Lane r < k records selection r with its rank among this workgroup's
+// selections of the same expert (LDS counter), and the workgroup's per-expert
+// counts go to wg_counts[E][workgroup].  Ranks only order rows inside an
+// expert's group.
+template <int NQ>
+__global__ __launch_bounds__(512) void router_topk_kernel(const float* __restrict__ parts, int n_split, int T, int E, int k,
+                                                           int group_tokens, int32_t* __restrict__ ids,
+                                                           float* __restrict__ wts, int32_t* __restrict__ pos,
+                                                           int32_t* __restrict__ wg_counts, float* __restrict__ logits) {
+    __shared__ int lcnt[64 * NQ];
+    const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+    for (int e = threadIdx.x; e < 64 * NQ; e += 512) lcnt[e] = 0;
+    __syncthreads();
+    const int t_end = min((int)(blockIdx.x + 1) * group_tokens, T);
+    const int64_t stride = (int64_t)T * E;
+    for (int t = blockIdx.x * group_tokens + wave; t < t_end; t += 8) {
+        float z[NQ], p[NQ];
+        uint32_t key[NQ];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const int e = lane + 64 * q;
-            kq[i][q] = e < EP ? keys[(wave * TPW + i) * EP + e] : 0;
-            rank[i][q] = 0;
+            const float* r = parts + (int64_t)t * E + min(e, E - 1);
+            float v;
+            if (n_split == 8)
+                v = ((r[0] + r[stride]) + (r[2 * stride] + r[3 * stride])) +
+                    ((r[4 * stride] + r[5 * stride]) + (r[6 * stride] + r[7 * stride]));
+            else if (n_split == 4)
+                v = (r[0] + r[stride]) + (r[2 * stride] + r[3 * stride]);
+            else if (n_split == 2)
+                v = r[0] + r[stride];
+            else
+                v = r[0];
+            if (logits && e < E) logits[(int64_t)t * E + e] = v;   // test hook
+            v = (e < E && v == v) ? v + 0.f : -INFINITY;           // (+0.f: -0 and +0 compare equal)
+            z[q] = v;
+            const uint32_t b = __float_as_uint(v);
+            key[q] = e < E ? b ^ ((b >> 31) ? 0xffffffffu : 0x80000000u) : 0u;   // 0: below every logit's key
         }
-#pragma unroll 8
-    for (int e2 = 0; e2 < EP; e2 += 2) {
+        float m = z[0];
 #pragma unroll
-        for (int i = 0; i < TPW; ++i) {
-            const uint64_t* kr = keys + (wave * TPW + i) * EP;
-            const uint64_t k0 = kr[e2], k1 = kr[e2 + 1];
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) rank[i][q] += (k0 > kq[i][q]) + (k1 > kq[i][q]);
-        }
-    }
-    for (int i = 0; i < TPW; ++i) {
-        const int tt = wave * TPW + i, t = t0 + tt;
-        const float* z = zs[0][tt];
-        float v[NQ];
-        float vm = -INFINITY;
+        for (int q = 1; q < NQ; ++q) m = fmaxf(m, z[q]);
+        m = wave_max_dpp(m);
+        float own = 0.f;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const int e = lane + 64 * q;
-            v[q] = e < E ? z[e] : -INFINITY;
-            vm = fmaxf(vm, v[q]);
-        }
-        const float m = wave_max_dpp(vm);
-        float p[NQ], own = 0.f;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            p[q] = (lane + 64 * q < E) ? __expf(v[q] - m) : 0.f;
+            p[q] = lane + 64 * q < E ? __expf(z[q] - m) : 0.f;
             own += p[q];
         }
         const float sum = wave_sum_dpp(own);
-        float psel = 0.f;
+        int sel = 0;
+        float w = 0.f;                               // lane r < k: exp(z - m) of selection r
+        for (int r = 0; r < k; ++r) {
+            uint32_t best = key[0];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
-            if (rank[i][q] < k) psel += p[q] / sum;
-        const float psum = wave_sum_dpp(psel);
-        if (t < T) {
+            for (int q = 1; q < NQ; ++q) best = key[q] > best ? key[q] : best;
+            best = wave_max_u32(best);
+            // first owner of the key: the lowest block that holds it, then its
+            // lowest lane (one of the ballots is not empty)
+            unsigned long long b = __ballot(key[NQ - 1] == best);
+            int qs = NQ - 1;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const int e = lane + 64 * q;
-                if (e < E && rank[i][q] < k) {
-                    const int64_t o = (int64_t)t * k + rank[i][q];
-                    ids[o] = e;
-                    wts[o] = p[q] / sum / psum;
-                    pos[o] = atomicAdd(&lcnt[e], 1);
-                }
+            for (int q = NQ - 2; q >= 0; --q) {
+                const unsigned long long bq = __ballot(key[q] == best);
+                qs = bq ? q : qs;
+                b = bq ? bq : b;
             }
+            const int l = (int)__builtin_ctzll(b);
+            float pq = p[0];
+#pragma unroll
+            for (int q = 1; q < NQ; ++q) pq = q == qs ? p[q] : pq;
+            const float pv = lane_value(pq, l);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) key[q] = (q == qs && lane == l) ? 0u : key[q];
+            sel = lane == r ? l + 64 * qs : sel;
+            w = lane == r ? pv : w;
+        }
+        w /= sum;
+        const float psum = wave_sum_dpp(w);
+        if (lane < k) {
+            const int64_t o = (int64_t)t * k + lane;
+            ids[o] = sel;
+            wts[o] = w / psum;
+            pos[o] = atomicAdd(&lcnt[sel], 1);
         }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < E; e += NW * 64) wg_counts[(int64_t)e * gridDim.x + blockIdx.x] = lcnt[e];
+    for (int e = threadIdx.x; e < E; e += 512) wg_counts[(int64_t)e * gridDim.x + blockIdx.x] = lcnt[e];
 }
 
 // Exclusive scan of n <= 512 non-negative ints held in LDS, by one wave;
@@ -238,118 +259,50 @@ __device__ void wave_scan512(const int* in, int* out, int n) {
     if (lane == 63) out[n] = incl;
 }
 
-// Dispatch plan (one workgroup of 16 waves).  The per-workgroup counts of
-// each routed expert e, wg_counts[e][0 .. nwg), become exclusive offsets over
-// the router workgroups (in place) and their total the group size: 16 threads
-// share an expert row, each summing a contiguous segment (loads issued eight
-// at a time), then a 16-lane scan gives each segment its start.  Groups are
-// the E routed experts followed by n_shared shared experts of T rows each;
-// their sizes are scanned into grp_off[0..G], and the tile table (group, m0)
-// of the grouped GEMM and its length are written.
-__global__ __launch_bounds__(1024) void dispatch_plan_kernel(int T, int E, int n_shared, int nwg, int bm,
-                                                             int32_t* __restrict__ wg_counts,
-                                                             int32_t* __restrict__ grp_off, int2* __restrict__ tile_tab,
-                                                             int32_t* __restrict__ n_tiles) {
-    __shared__ int cnt[512], off[513], ntl[512], toff[513];
-    const int G = E + n_shared;
-    const int wave = threadIdx.x >> 6, sub = threadIdx.x & 15, row = threadIdx.x >> 4;
-    const int seg = (nwg + 15) >> 4;
-    const int w0 = min(sub * seg, nwg), w1 = min(w0 + seg, nwg);
-    for (int e0 = 0; e0 < E; e0 += 64) {
-        const int e = e0 + row;
-        const bool live = e < E;
-        int32_t* col = wg_counts + (int64_t)(live ? e : 0) * nwg;
-        int s = 0;
-        if (live) {
-            for (int w = w0; w < w1; w += 8) {
-                int v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = w + u < w1 ? col[w + u] : 0;
-#pragma unroll
-                for (int u = 0; u < 8; ++u) s += v[u];
-            }
-        }
-        int incl = s;
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-            const int u = __shfl_up(incl, o, 16);
-            if (sub >= o) incl += u;
-        }
-        if (live) {
-            int run = incl - s;
-            for (int w = w0; w < w1; w += 8) {
-                int v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = w + u < w1 ? col[w + u] : 0;
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (w + u < w1) {
-                        col[w + u] = run;
-                        run += v[u];
-                    }
-            }
-            if (sub == 15) cnt[e] = incl;
-        }
-    }
-    for (int gi = E + threadIdx.x; gi < G; gi += blockDim.x) cnt[gi] = T;
-    __syncthreads();
-    for (int gi = threadIdx.x; gi < G; gi += blockDim.x) ntl[gi] = (cnt[gi] + bm - 1) / bm;
-    __syncthreads();
-    if (wave == 0) wave_scan512(cnt, off, G);
-    else if (wave == 1) wave_scan512(ntl, toff, G);
-    __syncthreads();
-    for (int gi = threadIdx.x; gi <= G; gi += blockDim.x) grp_off[gi] = off[gi];
-    if (threadIdx.x == 0) *n_tiles = toff[G];
-    for (int gi = threadIdx.x; gi < G; gi += blockDim.x)
-        for (int t = 0; t < ntl[gi]; ++t) tile_tab[toff[gi] + t] = make_int2(gi, t * bm);
-}
-
-// Fused dispatch for small count tables: one workgroup per router workgroup
-// w (its 32 tokens).  Each workgroup derives from the per-expert counts
-// wg_counts[E][nwg] what it needs itself: every group's size (all routed
-// experts, then n_shared shared experts of T rows) and, per expert, how many
-// of that expert's selections come from router workgroups before w (4
-// threads per expert row, each summing a contiguous segment).  Workgroup 0
-// also writes grp_off, the tile table and its length.  The selections of the
-// workgroup's tokens then get their rows as in dispatch_scatter_kernel.  No
-// workgroup waits for another; the redundant reads of the count table
-// (E * nwg ints per workgroup) are why this is used for small tables only.
-__global__ __launch_bounds__(256) void dispatch_fused_kernel(const int32_t* __restrict__ ids, int T, int k, int E,
-                                                              int n_shared, int nwg, int bm,
-                                                              const int32_t* __restrict__ wg_counts,
-                                                              int32_t* __restrict__ grp_off,
-                                                              int2* __restrict__ tile_tab,
-                                                              int32_t* __restrict__ n_tiles,
-                                                              int32_t* __restrict__ slot, int32_t* __restrict__ a_rows) {
+// Dispatch: one workgroup per router workgroup w (its group_tokens tokens).
+// Each workgroup derives from the per-expert counts wg_counts[E][nwg] what it
+// needs itself: every group's size (all routed experts, then n_shared shared
+// experts of T rows) and, per expert, how many of that expert's selections come
+// from router workgroups before w (1024 / (64 NQ) threads per expert row, E <=
+// 64 NQ, consecutive threads on consecutive counts, 16 loads at a time).  Workgroup 0 also writes grp_off, the tile table
+// (group, m0) of the grouped GEMM and its length.  The selections of the
+// workgroup's tokens then get their rows: slot (in place of the rank) =
+// grp_off[e] + those before w + rank, a_rows[slot] = token.  No workgroup waits
+// for another; every one reads the whole table, so the host makes the groups
+// large enough to keep it small (router_group_tokens).
+template <int NQ>
+__global__ __launch_bounds__(1024) void dispatch_kernel(const int32_t* __restrict__ ids, int T, int k, int E,
+                                                       int n_shared, int nwg, int group_tokens, int bm,
+                                                       const int32_t* __restrict__ wg_counts,
+                                                       int32_t* __restrict__ grp_off, int2* __restrict__ tile_tab,
+                                                       int32_t* __restrict__ n_tiles, int32_t* __restrict__ slot,
+                                                       int32_t* __restrict__ a_rows) {
     __shared__ int tot[512], before[512], off[513], ntl[512], toff[513];
     const int w = blockIdx.x, G = E + n_shared;
-    const int wave = threadIdx.x >> 6, q = threadIdx.x & 3, er = threadIdx.x >> 2;
-    const int seg = (nwg + 3) >> 2;
-    const int w0 = min(q * seg, nwg), w1 = min(w0 + seg, nwg);
-    for (int e0 = 0; e0 < E; e0 += 64) {
-        const int e = e0 + er;
-        int s_all = 0, s_pre = 0;
-        if (e < E) {
-            const int32_t* col = wg_counts + (int64_t)e * nwg;
-            for (int v0 = w0; v0 < w1; v0 += 8) {
-                int c[8];
+    constexpr int TPR = 16 / NQ;                     // threads per expert row
+    const int wave = threadIdx.x >> 6, q = threadIdx.x % TPR, e = threadIdx.x / TPR;
+    int s_all = 0, s_pre = 0;
+    if (e < E) {
+        const int32_t* col = wg_counts + (int64_t)e * nwg;
+        for (int v0 = q; v0 < nwg; v0 += 16 * TPR) {
+            int c[16];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) c[u] = v0 + u < w1 ? col[v0 + u] : 0;
+            for (int u = 0; u < 16; ++u) c[u] = v0 + u * TPR < nwg ? col[v0 + u * TPR] : 0;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    s_all += c[u];
-                    if (v0 + u < w) s_pre += c[u];
-                }
+            for (int u = 0; u < 16; ++u) {
+                s_all += c[u];
+                if (v0 + u * TPR < w) s_pre += c[u];
             }
         }
-        s_all += __shfl_xor(s_all, 1, 64);
-        s_all += __shfl_xor(s_all, 2, 64);
-        s_pre += __shfl_xor(s_pre, 1, 64);
-        s_pre += __shfl_xor(s_pre, 2, 64);
-        if (e < E && q == 0) {
-            tot[e] = s_all;
-            before[e] = s_pre;
-        }
+    }
+#pragma unroll
+    for (int o = 1; o < TPR; o <<= 1) {
+        s_all += __shfl_xor(s_all, o, 64);
+        s_pre += __shfl_xor(s_pre, o, 64);
+    }
+    if (e < E && q == 0) {
+        tot[e] = s_all;
+        before[e] = s_pre;
     }
     for (int gi = E + threadIdx.x; gi < G; gi += blockDim.x) tot[gi] = T;
     __syncthreads();
@@ -364,40 +317,18 @@ __global__ __launch_bounds__(256) void dispatch_fused_kernel(const int32_t* __re
         for (int gi = threadIdx.x; gi < G; gi += blockDim.x)
             for (int t = 0; t < ntl[gi]; ++t) tile_tab[toff[gi] + t] = make_int2(gi, t * bm);
     }
-    const int t0 = w * 32;
-    for (int il = threadIdx.x; il < 32 * k; il += blockDim.x) {
-        const int t = t0 + il / k;
-        if (t < T) {
-            const int64_t i = (int64_t)t0 * k + il;
-            const int e = ids[i];
-            const int sr = off[e] + before[e] + slot[i];
-            slot[i] = sr;
-            a_rows[sr] = t;
-        }
+    const int t0 = w * group_tokens;
+    const int nt = min(group_tokens, T - t0);
+    for (int il = threadIdx.x; il < nt * k; il += blockDim.x) {
+        const int64_t i = (int64_t)t0 * k + il;
+        const int ei = ids[i];
+        const int sr = off[ei] + before[ei] + slot[i];
+        slot[i] = sr;
+        a_rows[sr] = t0 + il / k;
     }
-    for (int il = threadIdx.x; il < 32 * n_shared; il += blockDim.x) {
-        const int t = t0 + (il & 31), sh = il >> 5;
-        if (t < T) a_rows[off[E + sh] + t] = t;
-    }
-}
-
-// Thread i < T*k turns the rank pos[i] of selection i into its row
-// slot[i] = grp_off[e] + (offset of its router workgroup at e) + pos[i]
-// (in place) and sets a_rows[slot] = token; the rest fill the shared groups.
-__global__ __launch_bounds__(256) void dispatch_scatter_kernel(const int32_t* __restrict__ ids, int T, int k, int E,
-                                                               int n_shared, int nwg, const int32_t* __restrict__ wg_off,
-                                                               const int32_t* __restrict__ grp_off,
-                                                               int32_t* __restrict__ slot, int32_t* __restrict__ a_rows) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nr = T * k;
-    if (i < nr) {
-        const int t = i / k, e = ids[i];
-        const int s = grp_off[e] + wg_off[(int64_t)e * nwg + (t >> 5)] + slot[i];
-        slot[i] = s;
-        a_rows[s] = t;
-    } else if (i < nr + n_shared * T) {
-        const int r = i - nr, sh = r / T, t = r - sh * T;
-        a_rows[grp_off[E + sh] + t] = t;
+    for (int il = threadIdx.x; il < nt * n_shared; il += blockDim.x) {
+        const int t = t0 + il % nt, sh = il / nt;
+        a_rows[off[E + sh] + t] = t;
     }
 }
 
@@ -457,65 +388,77 @@ __global__ void combine_kernel(float* __restrict__ x, const bf16_t* __restrict__
     if (g_next) rms_store_row(xr, g_next, h_next + (int64_t)t * d, d, block_rms_scale(ss, d, eps));
 }
 
-template <int NB>
-void launch_router_nb(int rowb, dim3 grid, hipStream_t st, const bf16_t* h, const bf16_t* Wr, int T, int d, int E,
-                      int k, int32_t* ids, float* w, int32_t* pos, int32_t* wg_counts, float* logits) {
-    if constexpr (NB <= 2) {
-        if (rowb == 512) {
-            hipLaunchKernelGGL((router_topk_kernel<NB, 512>), grid, dim3(512), 0, st, h, Wr, T, d, E, k, ids, w, pos,
-                               wg_counts, logits);
-            return;
-        }
-    }
-    if constexpr (NB <= 4) {
-        if (rowb == 256) {
-            hipLaunchKernelGGL((router_topk_kernel<NB, 256>), grid, dim3(512), 0, st, h, Wr, T, d, E, k, ids, w, pos,
-                               wg_counts, logits);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((router_topk_kernel<NB, 128>), grid, dim3(512), 0, st, h, Wr, T, d, E, k, ids, w, pos,
-                       wg_counts, logits);
-}
-
 }  // namespace
 
-hipError_t launch_router_topk(const bf16_t* h, const bf16_t* Wr, int T, int d, int E, int k, int32_t* ids,
-                              float* w, int32_t* pos, int32_t* wg_counts, hipStream_t st, float* logits) {
-    if (E < 1 || E > 256 || k < 1 || k > 8 || k > E || d % 64 != 0 || T < 1) return hipErrorInvalidValue;
-    if ((int64_t)T * d * 2 >= ((int64_t)1 << 31)) return hipErrorInvalidValue;   // 32-bit buffer offsets into h
-    const dim3 grid((T + 31) / 32), block(512);
-    // The widest K chunk (256, 128 or 64 columns: 512, 256 or 128-byte LDS
-    // rows, so the fewest stage barriers) that divides d and whose three
-    // stages fit in the LDS with the expert rows.
-    const int nb = E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8;
-    const int rowb = nb <= 2 && d % 256 == 0 ? 512 : nb <= 4 && d % 128 == 0 ? 256 : 128;
-    if (E <= 32)
-        launch_router_nb<1>(rowb, grid, st, h, Wr, T, d, E, k, ids, w, pos, wg_counts, logits);
-    else if (E <= 64)
-        launch_router_nb<2>(rowb, grid, st, h, Wr, T, d, E, k, ids, w, pos, wg_counts, logits);
-    else if (E <= 128)
-        launch_router_nb<4>(rowb, grid, st, h, Wr, T, d, E, k, ids, w, pos, wg_counts, logits);
-    else
-        launch_router_nb<8>(rowb, grid, st, h, Wr, T, d, E, k, ids, w, pos, wg_counts, logits);
+int router_parts(int d) { return d % 512 == 0 ? 8 : d % 256 == 0 ? 4 : 2; }
+
+// Enough workgroups for two per CU; more only adds partial logits to write and
+// read back.
+int router_splits(int T, int d, int E, int64_t capacity) {
+    const int64_t wgs = (int64_t)((T + 63) / 64) * ((E + 63) / 64);
+    int n = router_parts(d);
+    while (n > 1 && (wgs * n > 512 || (int64_t)n * T * E * 4 > capacity)) n >>= 1;
+    return n;
+}
+
+// The top-k of a token is about 2000 cycles of a SIMD, so small groups spread
+// it (640 tokens of 64 experts: 20 groups of 32 take 6.4 us), but the dispatch
+// workgroups each read all groups' counts: at most 256 groups and 32768 counts
+// (at 32768 tokens of 64 experts, dispatch with the launch: 512 groups 45 us,
+// 256 groups 21; one workgroup planning 1024 groups, and a scatter: 116).
+int router_group_tokens(int T, int E, int least) {
+    const int64_t n = (T + least - 1) / least;
+    return least * (int)std::max<int64_t>((n + 255) / 256, (E * n + 32767) / 32768);
+}
+
+hipError_t launch_router_logits(const bf16_t* h, const bf16_t* Wr, int T, int d, int E, int n_split, float* parts,
+                                hipStream_t st) {
+    if (E < 1 || E > 256 || d % 128 != 0 || T < 1) return hipErrorInvalidValue;
+    const int np = router_parts(d);
+    if (n_split < 1 || np % n_split != 0) return hipErrorInvalidValue;
+    const dim3 grid((T + 63) / 64, (E + 63) / 64, n_split);
+#define ROUTER_CASE(CH)                                                                                       \
+    case CH:                                                                                                  \
+        hipLaunchKernelGGL(router_logits_kernel<CH>, grid, dim3(256), 0, st, h, Wr, T, d, E, d / np, parts); \
+        break;
+    switch (np / n_split) {
+        ROUTER_CASE(1)
+        ROUTER_CASE(2)
+        ROUTER_CASE(4)
+        ROUTER_CASE(8)
+        default:
+            return hipErrorInvalidValue;
+    }
+#undef ROUTER_CASE
     return hipGetLastError();
 }
 
-hipError_t launch_dispatch(const int32_t* ids, int T, int k, int E, int n_shared, int bm, int32_t* wg_counts,
-                           int32_t* grp_off, int2* tile_tab, int32_t* n_tiles, int32_t* slot, int32_t* a_rows,
-                           hipStream_t st) {
-    if (E + n_shared > 512) return hipErrorInvalidValue;
-    const int nwg = (T + 31) / 32;
-    if ((int64_t)E * nwg <= 16384) {
-        hipLaunchKernelGGL(dispatch_fused_kernel, dim3(nwg), dim3(256), 0, st, ids, T, k, E, n_shared, nwg, bm,
-                           wg_counts, grp_off, tile_tab, n_tiles, slot, a_rows);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(dispatch_plan_kernel, dim3(1), dim3(1024), 0, st, T, E, n_shared, nwg, bm, wg_counts,
-                       grp_off, tile_tab, n_tiles);
-    const int64_t n = (int64_t)T * k + (int64_t)n_shared * T;
-    hipLaunchKernelGGL(dispatch_scatter_kernel, dim3((unsigned)std::max<int64_t>(1, (n + 255) / 256)), dim3(256), 0,
-                       st, ids, T, k, E, n_shared, nwg, wg_counts, grp_off, slot, a_rows);
+hipError_t launch_router_topk(const float* parts, int n_split, int T, int E, int k, int group_tokens, int32_t* ids, float* w,
+                              int32_t* pos, int32_t* wg_counts, hipStream_t st, float* logits) {
+    if (group_tokens < 1 || E < 1 || E > 256 || k < 1 || k > 8 || k > E || T < 1) return hipErrorInvalidValue;
+    if (n_split != 1 && n_split != 2 && n_split != 4 && n_split != 8) return hipErrorInvalidValue;
+    const int gt = group_tokens;
+    const dim3 grid((T + gt - 1) / gt), block(512);
+    if (E <= 64)
+        hipLaunchKernelGGL(router_topk_kernel<1>, grid, block, 0, st, parts, n_split, T, E, k, gt, ids, w, pos, wg_counts,
+                           logits);
+    else if (E <= 128)
+        hipLaunchKernelGGL(router_topk_kernel<2>, grid, block, 0, st, parts, n_split, T, E, k, gt, ids, w, pos, wg_counts,
+                           logits);
+    else
+        hipLaunchKernelGGL(router_topk_kernel<4>, grid, block, 0, st, parts, n_split, T, E, k, gt, ids, w, pos, wg_counts,
+                           logits);
+    return hipGetLastError();
+}
+
+hipError_t launch_dispatch(const int32_t* ids, int T, int k, int E, int n_shared, int group_tokens, int bm,
+                           const int32_t* wg_counts, int32_t* grp_off, int2* tile_tab, int32_t* n_tiles,
+                           int32_t* slot, int32_t* a_rows, hipStream_t st) {
+    if (E + n_shared > 512 || group_tokens < 1) return hipErrorInvalidValue;
+    const int gt = group_tokens, nwg = (T + gt - 1) / gt;
+    auto* kernel = E <= 64 ? dispatch_kernel<1> : E <= 128 ? dispatch_kernel<2> : dispatch_kernel<4>;
+    hipLaunchKernelGGL(kernel, dim3(nwg), dim3(1024), 0, st, ids, T, k, E, n_shared, nwg, gt, bm, wg_counts, grp_off,
+                       tile_tab, n_tiles, slot, a_rows);
     return hipGetLastError();
 }
 

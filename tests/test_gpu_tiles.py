@@ -7,6 +7,8 @@ from __future__ import annotations
 import pytest
 
 from tests.gpu_util import log, need_gpu
+from tests.test_gpu_sweep import _check
+from workloads import MODELS
 
 pytestmark = pytest.mark.gpu
 
@@ -22,6 +24,11 @@ SHAPES = {
                       expert_ffn_dim=192, n_shared_experts=1),
     "moe_hd64_no_shared": dict(BASE, d_model=384, n_heads=6, n_kv_heads=2, head_dim=64, ffn_dim=0, n_experts=5,
                                top_k=1, expert_ffn_dim=64, n_shared_experts=0),
+    # logit rows longer than what the expert products write (partial logits go elsewhere)
+    "moe_256_narrow": dict(BASE, d_model=128, n_heads=2, n_kv_heads=2, head_dim=64, ffn_dim=0, n_experts=256, top_k=1,
+                           expert_ffn_dim=64, n_shared_experts=0),
+    "moe_130": dict(BASE, d_model=512, n_heads=4, n_kv_heads=2, head_dim=64, ffn_dim=0, n_experts=130, top_k=8,
+                    expert_ffn_dim=64, n_shared_experts=1),
 }
 
 
@@ -46,3 +53,18 @@ def test_rows_do_not_depend_on_the_batch(name, seq):
         lone = r.debug_layer(0, x[(b - 1) * seq:b * seq].clone(), 1, seq)
         assert torch.equal(y[-seq:], lone), f"last row of batch {b}"
     log(f"[tiles {name} seq {seq}] batches {batches} equal the sequence alone")
+
+
+@pytest.mark.parametrize("over,B,P,D", [
+    # router with 2, 4 and 8 K parts, 2 and 4 expert blocks of 64, few and many tokens per group
+    (dict(d_model=128, n_heads=2, n_kv_heads=2, head_dim=64, n_experts=256, top_k=1, expert_ffn_dim=64,
+          n_shared_experts=0), 2, 3, 30),
+    (dict(d_model=640, n_heads=5, n_kv_heads=5, head_dim=128, n_experts=130, top_k=8, expert_ffn_dim=64,
+          n_shared_experts=1), 1, 40, 25),
+    (dict(d_model=768, n_heads=6, n_kv_heads=2, head_dim=128, n_experts=65, top_k=3, expert_ffn_dim=128,
+          n_shared_experts=1), 1, 0, 65),
+    (dict(d_model=512, n_heads=4, n_kv_heads=2, head_dim=64, n_experts=200, top_k=8, expert_ffn_dim=64,
+          n_shared_experts=0), 5, 100, 333),
+])
+def test_router_against_the_oracle(over, B, P, D):
+    _check(MODELS["tiny"].replace(n_layers=1, ffn_dim=0, vocab=500, **over), B, P, D, 91, f"router {over['n_experts']}")
