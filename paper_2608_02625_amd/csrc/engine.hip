@@ -450,7 +450,7 @@ GemmTile expert_tile(const dlm_config& c, int64_t T) {
     const double rows = (double)T * c.top_k / c.n_experts;
     const int64_t narrow = G * ((2 * (int64_t)c.expert_ffn_dim + 127) / 128);
     if (rows <= 40 || (rows <= 72 && narrow <= 2048)) return {64, 128, 3};
-    if (rows <= 128) return {128, 128, 3};
+    if (rows <= (narrow <= 2048 ? 128 : 64)) return {128, 128, 3};
     return {256, 256, 11};
 }
 

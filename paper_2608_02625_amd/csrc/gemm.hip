@@ -182,7 +182,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     // by neighbouring tiles stay in that XCD's L2.
     const int tiles_m_or_listed = GROUPED ? *a.n_tiles : (a.M + BM - 1) / BM;
     const int total = tiles_m_or_listed * tiles_n;
-    const int chunk = (total + 7) >> 3;
+    // (a multiple of 4: bands of 2 or 4 row tiles stay on one XCD and in one round)
+    const int chunk = GROUPED ? (((total + 7) >> 3) + 3) & ~3 : (total + 7) >> 3;
     const int x_end = min(((int)blockIdx.x & 7) * chunk + chunk, total);
     const int stride = (int)gridDim.x >> 3;
     int L = ((int)blockIdx.x & 7) * chunk + ((int)blockIdx.x >> 3);
@@ -191,10 +192,30 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
         int g, m0, row_base, rows, n0;
     };
     auto decode = [&](int L) {
-        int ti, tn;
-        if (GROUPED || a.group_m <= 1) {
-            ti = L / tiles_n;
-            tn = L - ti * tiles_n;
+        TileIdx t;
+        int tn;
+        if constexpr (GROUPED) {
+            // The tile table and group offsets are read-only for the whole
+            // launch: scalar loads, no wait behind copies in flight.  A raster
+            // band of row tiles of one group is walked down its columns, so
+            // that the workgroups that share a slice of the group's weights run
+            // at the same time and fetch it once (packing: kRasterBand).  The
+            // row tiles of a group have equal heights: as tiles of 256 rows and
+            // a short last one, the sharing workgroups drifted apart.  257
+            // groups of 320 rows, d 4096: 12.7 GB fetched for gate/up row by
+            // row, 11.1 by columns, 8.4 with equal heights (7.2 is the least);
+            // gate/up 2370 -> 2180 us, down 1560 -> 1310; at 640 rows, d 2048,
+            // 336 -> 328 and 199 -> 185.
+            const int at = L / tiles_n;
+            const int* tab = reinterpret_cast<const int*>(a.tile_tab) + 2 * at;
+            const int e = uniform(ld_const(tab));
+            const int pos = (e >> 10) & 63, size = (e >> 16) & 63, height = (e >> 22) * 32;
+            const int r = L - (at - pos) * tiles_n;
+            tn = r / size;
+            t.g = e & 1023;
+            t.m0 = uniform(ld_const(tab + 1)) + (r - tn * size - pos) * height;
+            t.row_base = uniform(ld_const(a.grp_off + t.g));
+            t.rows = min(uniform(ld_const(a.grp_off + t.g + 1)) - t.row_base, t.m0 + height);
         } else {
             const int tiles_m = tiles_m_or_listed;
             const int per_group = a.group_m * tiles_n;
@@ -202,21 +223,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
             const int first_m = grp * a.group_m;
             const int gsz = min(tiles_m - first_m, a.group_m);
             const int r = L - grp * per_group;
-            ti = first_m + r % gsz;
             tn = r / gsz;
-        }
-        TileIdx t;
-        if (GROUPED) {
-            // The tile table and group offsets are read-only for the whole
-            // launch: scalar loads, no wait behind copies in flight.
-            const int* tab = reinterpret_cast<const int*>(a.tile_tab) + 2 * ti;
-            t.g = uniform(ld_const(tab));
-            t.m0 = uniform(ld_const(tab + 1));
-            t.row_base = uniform(ld_const(a.grp_off + t.g));
-            t.rows = uniform(ld_const(a.grp_off + t.g + 1)) - t.row_base;
-        } else {
             t.g = 0;
-            t.m0 = ti * BM;
+            t.m0 = (first_m + r - tn * gsz) * BM;
             t.row_base = 0;
             t.rows = a.M;
         }
@@ -320,7 +329,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     // low 4 row bits only, so rows +32i share the lane's base offset.
     // Chunk 2ks + h of a row sits at byte ((2ks + h) ^ key) * 16 of the row,
     // i.e. at (slot-0 offset) ^ (ks * 32): one XOR per slot and operand.
-    const int fa0 = swz<CPR>(wm * T::WM + (lane & 31), lane >> 5);
+    int fa0 = swz<CPR>(wm * T::WM + (lane & 31), lane >> 5);
     const int fb0 = swz<CPR>(wn * T::WN + (lane & 31), lane >> 5);
     bf16x8 ra[T::KS][T::TM], rb[T::KS][T::TN];
     // Per-lane bases of the stages being read: fa_s = fa0 + stage * A_BYTES
@@ -330,24 +339,25 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
         fa_s = fa0 + st_a * T::A_BYTES;
         fb_s = B_BASE + fb0 + st_b * T::B_BYTES;
     };
-    auto read_slot = [&](int ks) {                               // fragments of step ks
-        const int fa = fa_s ^ (ks * 32), fb = fb_s ^ (ks * 32);
+    auto read_a = [&](int ks, int i) __attribute__((always_inline)) {            // A fragment of step ks, row block i
+        ra[ks][i] = *(lds_frag*)((lds_char*)lds + (fa_s ^ (ks * 32)) + i * 32 * T::ROW);
+    };
+    auto read_slot = [&](int ks) __attribute__((always_inline)) {                // fragments of step ks
+        const int fb = fb_s ^ (ks * 32);
 #pragma unroll
-        for (int i = 0; i < T::TM; ++i)
-            ra[ks][i] = *(lds_frag*)((lds_char*)lds + fa + i * 32 * T::ROW);
+        for (int i = 0; i < T::TM; ++i) read_a(ks, i);
 #pragma unroll
         for (int j = 0; j < T::TN; ++j)
             rb[ks][j] = *(lds_frag*)((lds_char*)lds + fb + j * 32 * T::ROW);
     };
-    // The SwiGLU epilogue, and the bf16 one under the ping-pong schedule, take
-    // the accumulators transposed (operands swapped): a lane then holds 4
-    // consecutive output columns of one row, stored as one 8-byte write (a
-    // quarter of the store instructions; under ping-pong the epilogue runs
-    // inside a memory phase, where that count matters).  The other epilogues
-    // keep rows in the accumulator's 4-element groups (consecutive lanes =
-    // consecutive columns: fully coalesced 2-row accesses; measured faster for
-    // the residual read-modify-write).
-    constexpr bool TACC = EPI == EPI_SWIGLU || (PP && EPI == EPI_BF16);
+    // The SwiGLU and bf16 epilogues take the accumulators transposed (operands
+    // swapped): a lane then holds 4 consecutive output columns of one row, and
+    // after an exchange of lane halves 16 (an eighth of the store instructions;
+    // under ping-pong the epilogue runs inside a memory phase, where that count
+    // matters).  The other epilogues keep rows in the accumulator's 4-element
+    // groups (consecutive lanes = consecutive columns: fully coalesced 2-row
+    // accesses; measured faster for the residual read-modify-write).
+    constexpr bool TACC = EPI == EPI_SWIGLU || EPI == EPI_BF16;
     auto mfmas = [&](int ks) {
 #pragma unroll
         for (int i = 0; i < T::TM; ++i)
@@ -360,7 +370,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     constexpr int PRE = T::KS / 2;          // fragment steps of a tile run before its barrier
 
     // ---------------------------------------------------------------- epilogues
-    auto epilogue = [&](const int m0, const int rows, const int row_base, const int n0) __attribute__((always_inline)) {
+    // wrow, blocks: first row of this wave in the tile and its 32-row blocks (of
+    // grouped tiles under the ping-pong schedule; otherwise WM rows each).
+    auto epilogue = [&](const int m0, const int rows, const int row_base, const int n0, const int wrow, const int blocks)
+                        __attribute__((always_inline)) {
         // TACC: acc[i][j][4q + r] holds C[row][col] with
         //   row = wm*WM + i*32 + lane%32,  col = wn*WN + j*32 + 8q + 4*(lane/32) + r.
         // otherwise acc[i][j][e] holds C[row][col] with
@@ -371,56 +384,38 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
         asm volatile("" : "+v"(lane));
         const int lrow0 = wm * T::WM + 4 * (lane >> 5);
         const int lcol0 = wn * T::WN + (lane & 31);
-        const int trow = m0 + wm * T::WM + (lane & 31);              // TACC row of block i = 0
-        const int tcol = n0 + wn * T::WN + 4 * (lane >> 5);          // TACC column of j = 0, q = 0
-        // 4-column groups are stored whole when they lie inside N and rows are
-        // 16-byte (f32) / 8-byte (bf16) aligned.
-        const bool vec = (a.ldo & 3) == 0;
+        const int trow = m0 + wrow + (lane & 31);                    // TACC row of block i = 0
         const bool full_tile = m0 + BM <= rows && n0 + BN <= a.N;
 
-        if constexpr (EPI == EPI_BF16 && TACC) {
+        if constexpr (EPI == EPI_BF16) {
             // Rows of 32-column blocks: after swap_halves16 a lane holds 16
             // consecutive columns of its row, stored as two 16-byte writes
             // (whole 32-byte runs: fewer partially written cache lines than
             // 8-byte stores, which the store path pays for per line).  The
             // exchange is done by every lane of the wave; rows past the end
-            // only skip their stores.
-            const bool wide = (a.ldo & 7) == 0;
+            // only skip their stores.  N is a multiple of 64 and rows are
+            // 16-byte aligned (checked on the host).
             const int half = lane >> 5;
 #pragma unroll
             for (int i = 0; i < T::TM; ++i) {
+                if (GROUPED && i >= blocks) continue;
                 const int r = trow + i * 32;
                 bf16_t* orow = reinterpret_cast<bf16_t*>(a.out) + (GROUPED ? (int64_t)row_base + r : r) * a.ldo;
 #pragma unroll
                 for (int j = 0; j < T::TN; ++j) {
                     const int cb = n0 + wn * T::WN + j * 32;           // first column of the block
-                    if (wide && cb + 32 <= a.N) {
-                        uint32_t p[4][2];
+                    if (cb >= a.N) continue;
+                    uint32_t p[4][2];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            p[q][0] = pack_bf16x2(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
-                            p[q][1] = pack_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-                        }
-                        swap_halves16(p);
-                        if (r < rows) {
-                            bf16_t* dst = orow + cb + 16 * half;
-                            *reinterpret_cast<u32x4*>(dst) = u32x4{p[0][0], p[0][1], p[2][0], p[2][1]};
-                            *reinterpret_cast<u32x4*>(dst + 8) = u32x4{p[1][0], p[1][1], p[3][0], p[3][1]};
-                        }
-                    } else if (r < rows) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int c = tcol + j * 32 + 8 * q;
-                            const float v[4] = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2],
-                                                acc[i][j][4 * q + 3]};
-                            if (vec && c + 3 < a.N) {
-                                *reinterpret_cast<u32x2*>(orow + c) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-                            } else {
-#pragma unroll
-                                for (int t = 0; t < 4; ++t)
-                                    if (c + t < a.N) orow[c + t] = f32_to_bf16(v[t]);
-                            }
-                        }
+                    for (int q = 0; q < 4; ++q) {
+                        p[q][0] = pack_bf16x2(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
+                        p[q][1] = pack_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+                    }
+                    swap_halves16(p);
+                    if (r < rows) {
+                        bf16_t* dst = orow + cb + 16 * half;
+                        *reinterpret_cast<u32x4*>(dst) = u32x4{p[0][0], p[0][1], p[2][0], p[2][1]};
+                        *reinterpret_cast<u32x4*>(dst + 8) = u32x4{p[1][0], p[1][1], p[3][0], p[3][1]};
                     }
                 }
             }
@@ -461,7 +456,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
                         }
                 }
             }
-        } else if constexpr (EPI == EPI_BF16 || EPI == EPI_F32 || EPI == EPI_F32_T) {
+        } else if constexpr (EPI == EPI_F32 || EPI == EPI_F32_T) {
 #pragma unroll
             for (int i = 0; i < T::TM; ++i)
 #pragma unroll
@@ -474,9 +469,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
                         const int c = n0 + lcol0 + j * 32;
                         if (c >= a.N) continue;
                         const float v = acc[i][j][e];
-                        if constexpr (EPI == EPI_BF16)
-                            reinterpret_cast<bf16_t*>(a.out)[orow * a.ldo + c] = f32_to_bf16(v);
-                        else if constexpr (EPI == EPI_F32)
+                        if constexpr (EPI == EPI_F32)
                             reinterpret_cast<float*>(a.out)[orow * a.ldo + c] = v;
                         else
                             reinterpret_cast<float*>(a.out)[(int64_t)c * a.ldo + orow] = v;
@@ -487,10 +480,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
             // gate and up values of the same 32 features.  As for the bf16 rows,
             // swap_halves16 gives each lane 16 consecutive features, stored as
             // two 16-byte writes.
-            const bool wide = (a.ldo & 7) == 0;
             const int half = lane >> 5;
 #pragma unroll
             for (int i = 0; i < T::TM; ++i) {
+                if (GROUPED && i >= blocks) continue;
                 const int r = trow + i * 32;
                 bf16_t* orow = reinterpret_cast<bf16_t*>(a.out) + (GROUPED ? (int64_t)row_base + r : r) * a.ldo;
 #pragma unroll
@@ -509,23 +502,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
                         p[q][0] = pack_bf16x2(hv[0], hv[1]);
                         p[q][1] = pack_bf16x2(hv[2], hv[3]);
                     }
-                    if (wide) {
-                        swap_halves16(p);
-                        if (r < rows) {
-                            bf16_t* dst = orow + (c0 >> 1) + 16 * half;
-                            *reinterpret_cast<u32x4*>(dst) = u32x4{p[0][0], p[0][1], p[2][0], p[2][1]};
-                            *reinterpret_cast<u32x4*>(dst + 8) = u32x4{p[1][0], p[1][1], p[3][0], p[3][1]};
-                        }
-                    } else if (r < rows) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int f = (c0 >> 1) + 8 * q + 4 * half;
-#pragma unroll
-                            for (int t = 0; t < 2; ++t) {
-                                orow[f + 2 * t] = (bf16_t)(p[q][t] & 0xffff);
-                                orow[f + 2 * t + 1] = (bf16_t)(p[q][t] >> 16);
-                            }
-                        }
+                    swap_halves16(p);
+                    if (r < rows) {
+                        bf16_t* dst = orow + (c0 >> 1) + 16 * half;
+                        *reinterpret_cast<u32x4*>(dst) = u32x4{p[0][0], p[0][1], p[2][0], p[2][1]};
+                        *reinterpret_cast<u32x4*>(dst + 8) = u32x4{p[1][0], p[1][1], p[3][0], p[3][1]};
                     }
                 }
             }
@@ -691,7 +672,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
             // the accumulators are never cleared separately; it is multiplied
             // even by a wave with no rows in the tile, which keeps no older
             // accumulator live.
-            auto compute = [&](auto first_tag) __attribute__((always_inline)) {
+            auto compute = [&](auto first_tag, int i0, int i1) __attribute__((always_inline)) {   // row blocks i0 .. i1 - 1
                 constexpr bool FIRST = decltype(first_tag)::value;
 #pragma unroll
                 for (int ks = 0; ks < T::KS; ++ks)
@@ -699,20 +680,40 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
                     for (int i = 0; i < T::TM; ++i)
 #pragma unroll
                         for (int j = 0; j < T::TN; ++j) {
+                            if (i < i0 || i >= i1) continue;
                             const f32x16 c = (FIRST && ks == 0) ? f32x16{} : acc[i][j];
                             acc[i][j] = TACC ? mfma32x32x16(rb[ks][j], ra[ks][i], c)
                                              : mfma32x32x16(ra[ks][i], rb[ks][j], c);
                         }
             };
-            // A wave whose rows all lie past the end of a grouped tile's rows
+            // The 32-row blocks of a grouped tile's rows are shared by its two
+            // wave rows, the first taking the odd one: fewer rows are fewer
+            // MFMAs and fragment reads for both.  (With the fixed rows 0-127 /
+            // 128-255 the first wave row would keep full phases until the tile
+            // is half empty.)  A wave row without any (tiles of up to 32 rows)
             // skips its MFMAs but still copies, reads and meets every barrier.
-            auto active = [&](const TileIdx& t) { return !GROUPED || t.m0 + wm * T::WM < t.rows; };
+            // 128 rows per expert at d 4096 (4096 tokens): 1273 -> 1244 us
+            // against shares in steps of 64 rows; 158 rows at d 2048: gate/up
+            // 173 -> 164, down 94 -> 84 against the fixed halves.
+            struct Share {
+                int n, row;                     // row blocks of this wave row, its first row in the tile
+            };
+            auto share_of = [&](const TileIdx& t) {
+                if (!GROUPED) return Share{T::TM, wm * T::WM};
+                const int total = min((t.rows - t.m0 + 31) >> 5, 2 * T::TM), first = (total + 1) >> 1;
+                return G == 0 ? Share{first, 0} : Share{total - first, first * 32};
+            };
 
             TileIdx cur = decode(L), prv = cur;
-            bool act = active(cur);
+            Share own = share_of(cur), prv_own = own;
+            fa0 = swz<CPR>(own.row + (lane & 31), lane >> 5);
             bool pend = false;                  // tile prv awaits its epilogue (stored in K step 0)
             int sa = 0, sb = 0;                 // stages of the next K tile to read
             bool fresh = true;                  // the current tile began with a prologue
+            auto turn = [&]() __attribute__((always_inline)) {         // cur is another tile
+                own = share_of(cur);
+                fa0 = swz<CPR>(own.row + (lane & 31), lane >> 5);
+            };
             start(cur);
             wait_vmcnt<NI * (S - 1)>();         // own part of K tile 0 landed
             lds_barrier();
@@ -722,79 +723,107 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
                 const bool more = L_next < x_end;
                 const TileIdx nxt = more ? decode(L_next) : cur;
                 const bool flow = cont && more;
-                // One K tile: copy local K tile x (x < 0: none) into the stage
-                // of K tile kt-1, read K tile kt, barrier, multiply, barrier.
+                // Copies issued in K step kt fetch K tile kt-1+S.  With
+                // continuous copies, those past the end fetch the next tile's
+                // first K tiles (its offsets are set up before them);
+                // otherwise they repeat the last K tile into a stage that is
+                // never read, which keeps every wait count constant.
+                const int kt_sw = flow ? nk + 1 - S : nk;
                 // K step 0 of a tile that follows another without a drain also
                 // stores that tile in its memory phase: a store-only epilogue
                 // after the copy (and, for group 1, after its wait, so that the
                 // stores are newer than every copy awaited before the next
                 // phase), one that also loads before the copy.
                 constexpr bool EPI_LOADS = EPI == EPI_RESID || EPI == EPI_QKV;
-                auto step = [&](int kt, int x, auto first_tag) __attribute__((always_inline)) {
+                int x0 = fresh ? -1 : min(S - 1, nk - 1);
+                bool waited = false;
+                auto copy_before = [&](int kt) { copy(kt, (CA ? sa : sb) == 0 ? S - 1 : (CA ? sa : sb) - 1); };
+                if (pend) {
+                    if constexpr (!EPI_LOADS) {
+                        copy_before(x0);
+                        x0 = -1;
+                        if constexpr (G == 1) wait_vmcnt<NI * (S - 2)>();   // own part of K tile 1 landed
+                        waited = true;
+                    }
+                    sched_fence();
+                    epilogue(prv.m0, prv.rows, prv.row_base, prv.n0, prv_own.row, prv_own.n);
+                    sched_fence();
+                    pend = false;
+                }
+                // One K tile: copy local K tile x (x < 0: none) into the stage
+                // of K tile kt-1, read K tile kt, barrier, multiply, barrier.
+                auto step = [&](int x, auto first_tag) __attribute__((always_inline)) {
                     constexpr bool FIRST = decltype(first_tag)::value;
                     // ---- memory phase
-                    const int so = CA ? sa : sb;                        // own stage of K tile kt
-                    bool waited = false;
-                    if constexpr (FIRST && EPI_LOADS) {
-                        // An epilogue that loads must not wait behind this
-                        // phase's copies: it runs before them.
-                        if (pend) {
-                            epilogue(prv.m0, prv.rows, prv.row_base, prv.n0);
-                            sched_fence();
-                            pend = false;
-                        }
-                    }
-                    if (x >= 0) copy(x, so == 0 ? S - 1 : so - 1);
-                    if constexpr (FIRST && !EPI_LOADS) {
-                        if (pend) {
-                            if constexpr (G == 1) wait_vmcnt<NI * (S - 2)>();   // own part of K tile 1 landed
-                            sched_fence();
-                            epilogue(prv.m0, prv.rows, prv.row_base, prv.n0);
-                            sched_fence();
-                            pend = false;
-                            waited = true;
-                        }
-                    }
+                    if (x >= 0) copy_before(x);
                     set_stage(sa, sb);
+                    if constexpr (GROUPED) {
 #pragma unroll
-                    for (int ks = 0; ks < T::KS; ++ks) read_slot(ks);
+                        for (int ks = 0; ks < T::KS; ++ks) {
+#pragma unroll
+                            for (int j = 0; j < T::TN; ++j)
+                                rb[ks][j] = *(lds_frag*)((lds_char*)lds + (fb_s ^ (ks * 32)) + j * 32 * T::ROW);
+                            read_a(ks, 0);
+                        }
+                        if (own.n > 1) {
+#pragma unroll
+                            for (int ks = 0; ks < T::KS; ++ks) read_a(ks, 1);
+                        }
+                        if (own.n > 2) {
+#pragma unroll
+                            for (int ks = 0; ks < T::KS; ++ks) read_a(ks, 2);
+                        }
+                        if (own.n > 3) {
+#pragma unroll
+                            for (int ks = 0; ks < T::KS; ++ks) read_a(ks, 3);
+                        }
+                    } else {
+#pragma unroll
+                        for (int ks = 0; ks < T::KS; ++ks) read_slot(ks);
+                    }
                     sa = sa + 1 == SA ? 0 : sa + 1;
                     sb = sb + 1 == SB ? 0 : sb + 1;
                     if constexpr (G == 1) {
-                        if (!waited) wait_vmcnt<NI * (S - 2)>();        // own part of K tile kt+1 landed
+                        if (!FIRST || !waited) wait_vmcnt<NI * (S - 2)>();       // own part of K tile kt+1 landed
                     }
                     sched_fence();
                     lds_barrier();
                     // ---- compute phase
-                    if (FIRST || act) compute(first_tag);
+                    if constexpr (GROUPED) {
+                        if (FIRST || own.n > 0) {
+                            compute(first_tag, 0, 1);
+                            if (own.n > 1) compute(first_tag, 1, 2);
+                            if (own.n > 2) compute(first_tag, 2, 3);
+                            if (own.n > 3) compute(first_tag, 3, 4);
+                        }
+                    } else {
+                        compute(first_tag, 0, T::TM);
+                    }
                     sched_fence();
-                    if constexpr (G == 0) wait_vmcnt<NI * (S - 2)>();   // own part of K tile kt+1 landed
+                    if constexpr (G == 0) wait_vmcnt<NI * (S - 2)>();            // own part of K tile kt+1 landed
                     lds_barrier();
                     sched_fence();
                 };
-                // Copies issued in K step kt fetch K tile kt-1+S.  With
-                // continuous copies, those past the end fetch the next tile's
-                // first K tiles (its offsets are set up between the two loops);
-                // otherwise they repeat the last K tile into a stage that is
-                // never read, which keeps every wait count constant.
-                const int kt_sw = flow ? nk + 1 - S : nk;
-                step(0, fresh ? -1 : min(S - 1, nk - 1), std::true_type());
-                for (int kt = 1; kt < kt_sw; ++kt) step(kt, min(kt - 1 + S, nk - 1), std::false_type());
+                step(x0, std::true_type());
+                for (int kt = 1; kt < kt_sw; ++kt) step(min(kt - 1 + S, nk - 1), std::false_type());
                 if (flow) {
                     setup(nxt);
 #pragma unroll
-                    for (int c = 0; c < S - 1; ++c) step(kt_sw + c, c, std::false_type());
+                    for (int c = 0; c < S - 1; ++c) step(c, std::false_type());
+                }
+                if (flow) {
                     prv = cur;
+                    prv_own = own;
                     pend = true;
                     cur = nxt;
                     L = L_next;
-                    act = active(cur);
+                    turn();
                     fresh = false;
                     continue;
                 }
                 // Drain: group 0 stores while group 1 multiplies its last K
                 // tile (one more barrier for group 0), then group 1 stores.
-                epilogue(cur.m0, cur.rows, cur.row_base, cur.n0);
+                epilogue(cur.m0, cur.rows, cur.row_base, cur.n0, own.row, own.n);
                 if constexpr (G == 0) __syncthreads();
                 if (!more) break;
                 // Short K (no continuous copies): every copy lands before the
@@ -803,7 +832,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
                 __syncthreads();
                 cur = nxt;
                 L = L_next;
-                act = active(cur);
+                turn();
                 sa = sb = 0;
                 fresh = true;
                 start(cur);
@@ -952,7 +981,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
         }
     }
 
-    epilogue(m0, rows, row_base, n0);
+    epilogue(m0, rows, row_base, n0, wm * T::WM, T::TM);
     if (!more) break;
     cur = nxt;
     L = L_next;
@@ -1070,6 +1099,9 @@ hipError_t launch_f32(const GemmArgs& a, int bm, int bn, hipStream_t st) {
 hipError_t launch_gemm(const GemmArgs& a, int epi, bool grouped, int bm, int bn, int max_tiles,
                        hipStream_t st) {
     if (a.K % 64 != 0 || a.N <= 0 || (!grouped && a.M <= 0)) return hipErrorInvalidValue;
+    // 16-byte row stores of whole 32-column blocks (64 interleaved ones under SwiGLU)
+    if ((epi == EPI_BF16 || epi == EPI_SWIGLU) && (a.N % 64 != 0 || a.ldo % 8 != 0 || (uintptr_t)a.out % 16 != 0))
+        return hipErrorInvalidValue;
     switch (epi) {
         case EPI_BF16:
             return grouped ? launch_pass<EPI_BF16, true>(a, bm, bn, max_tiles, st) : hipErrorInvalidValue;

@@ -32,6 +32,12 @@ enum GemmEpilogue {
     EPI_F32_T = 6,    // out_f32[col][row] (transposed store)
 };
 
+// Row tiles of a group are listed in order, all of one height (a multiple of
+// 32 up to the tile's), and rastered in bands of at most this many; an entry is
+// (group | position in its band << 10 | row tiles of the band << 16 | height /
+// 32 << 22, first row in the group).
+constexpr int kRasterBand = 4;
+
 struct GemmArgs {
     // C[M x N] = A[M x K] * B[N x K]^T  (bf16 in, fp32 accumulate)
     const bf16_t* A;
@@ -41,7 +47,7 @@ struct GemmArgs {
     int64_t b_group_stride;   // elements between consecutive groups' B (grouped mode)
     int M, N, K;
     // grouped mode (experts): tiles listed on the device
-    const int2* tile_tab;     // [max_tiles] (group, m0)
+    const int2* tile_tab;     // [max_tiles] row tiles, see kRasterBand
     const int* n_tiles;       // device scalar: valid entries in tile_tab
     const int* grp_off;       // [groups+1] row offsets (exclusive scan of group sizes)
     const int* a_rows;        // optional gather: A row of permuted row r (NULL = identity)

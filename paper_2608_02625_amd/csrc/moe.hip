@@ -315,7 +315,12 @@ __global__ __launch_bounds__(1024) void dispatch_kernel(const int32_t* __restric
         for (int gi = threadIdx.x; gi <= G; gi += blockDim.x) grp_off[gi] = off[gi];
         if (threadIdx.x == 0) *n_tiles = toff[G];
         for (int gi = threadIdx.x; gi < G; gi += blockDim.x)
-            for (int t = 0; t < ntl[gi]; ++t) tile_tab[toff[gi] + t] = make_int2(gi, t * bm);
+            for (int t = 0; t < ntl[gi]; ++t) {
+                const int pos = t % kRasterBand, size = min(ntl[gi] - (t - pos), kRasterBand);
+                // equal heights, in steps of 32 rows, that fit the group in its tiles
+                const int height = ((tot[gi] + ntl[gi] - 1) / ntl[gi] + 31) & ~31;
+                tile_tab[toff[gi] + t] = make_int2(gi | pos << 10 | size << 16 | (height >> 5) << 22, t * height);
+            }
     }
     const int t0 = w * group_tokens;
     const int nt = min(group_tokens, T - t0);

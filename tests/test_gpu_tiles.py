@@ -68,3 +68,23 @@ def test_rows_do_not_depend_on_the_batch(name, seq):
 ])
 def test_router_against_the_oracle(over, B, P, D):
     _check(MODELS["tiny"].replace(n_layers=1, ffn_dim=0, vocab=500, **over), B, P, D, 91, f"router {over['n_experts']}")
+
+
+@pytest.mark.parametrize("experts,shared", [(3, 0), (8, 1)])
+def test_rows_of_every_expert_tile_height(experts, shared):
+    """With top-k = E every expert gets every row: the row counts walk over the
+    heights of the expert tiles (steps of 32 rows, one to five tiles), and each
+    row must equal what it gets in a small batch."""
+    need_gpu()
+    import torch
+    from paper_2608_02625_amd import Refiner
+    shape = dict(BASE, d_model=512, n_heads=4, n_kv_heads=2, head_dim=64, ffn_dim=0, n_experts=experts, top_k=experts,
+                 expert_ffn_dim=320, n_shared_experts=shared)
+    r = Refiner(shape, 3)
+    x = torch.randn(1300, 512, generator=torch.Generator().manual_seed(5)).cuda()
+    ref = torch.cat([r.debug_layer(0, x[i:i + 26].clone(), 26, 1) for i in range(0, 1300, 26)])
+    for t in (1, 2, 32, 33, 64, 65, 72, 73, 128, 129, 160, 161, 191, 193, 224, 225, 255, 256, 257, 288, 289, 320, 449,
+              512, 513, 545, 768, 769, 1024, 1025, 1300):
+        y = r.debug_layer(0, x[:t].clone(), t, 1)
+        assert torch.equal(y, ref[:t]), f"{t} rows"
+    log(f"[expert tile heights E {experts} shared {shared}] equal")
