@@ -12,7 +12,9 @@
 // the block-causal mask for a window that is one block or the prompt.  A
 // window may also hold the finished block before the current one: its first
 // q_split query rows then see only the first n_keys_lo keys (up to their own
-// block's end), the others all n_keys.
+// block's end), the others all n_keys.  Or it holds the prompt and several
+// blocks, or several blocks, each row seeing the keys up to its block's end
+// (`block`): limits grow with the row, so a workgroup stops at its last row's.
 //
 // One workgroup = 4 waves = 128 queries of one (batch, head); each wave owns 32
 // queries.  Per tile of KEYS keys, K [KEYS][hd] and V^T [hd][KEYS] are copied
@@ -73,7 +75,7 @@ __device__ __forceinline__ float xor32_sum(float v) {
 template <int HD, int KEYS, int WPE, int NS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void attn_kernel(const bf16_t* __restrict__ Q, const bf16_t* K,
                                                    const bf16_t* Vt, bf16_t* __restrict__ O, int Sq, int Skv,
-                                                   int n_keys, int q_split, int n_keys_lo, int H, int KV,
+                                                   int n_keys, int q_split, int n_keys_lo, int block, int H, int KV,
                                                    float scale_log2, uint32_t k_bytes, uint32_t v_bytes) {
     using C = AttnCfg<HD, KEYS>;
     static_assert(NS >= 2, "at least two K/V stages");
@@ -84,7 +86,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
     const int qb = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int kvh = h / (H / KV);
     const int q = qb * 128 + wave * 32 + j;
-    const int lim = q < q_split ? n_keys_lo : n_keys;   // keys this lane's query sees
+    const int first = n_keys - (Sq - q_split);          // keys before the rows from q_split on
+    auto limit = [&](int r) {                           // keys that row r sees
+        return r < q_split ? n_keys_lo : block ? min(n_keys, first + ((r - q_split) / block + 1) * block) : n_keys;
+    };
+    const int lim = limit(q);
     const int VS = vt_stride(Skv);
     const int wv = wave;
 
@@ -153,7 +159,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
     const int vfrag = C::K_BYTES + j * C::V_ROW;
     const int vkey = chunk_key<C::V_CPR>(j);
 
-    const int nkt = (n_keys + C::KEYS - 1) / C::KEYS;
+    const int nkt = (limit(min(qb * 128 + 127, Sq - 1)) + C::KEYS - 1) / C::KEYS;
     // Tiles kt .. kt + NS - 2 are in flight at the top of tile kt; copies past
     // the last tile repeat it into a stage that is never read, so that every
     // wait below counts the same number of copies.
@@ -279,10 +285,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
 
 hipError_t launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int B,
                             int Sq, int Skv, int n_keys, int H, int KV, int hd, hipStream_t st, int q_split,
-                            int n_keys_lo) {
+                            int n_keys_lo, int block) {
     if (Sq <= 0 || n_keys <= 0 || n_keys > Skv) return hipErrorInvalidValue;
     if (q_split < 0 || q_split > Sq || (q_split > 0 && (n_keys_lo < 1 || n_keys_lo > n_keys)))
         return hipErrorInvalidValue;
+    // limits must not fall from one row to the next
+    if (block < 0 || (block > 0 && n_keys - (Sq - q_split) < (q_split > 0 ? n_keys_lo : 0))) return hipErrorInvalidValue;
     const dim3 grid((Sq + 127) / 128, H, B);
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)hd);
     // byte sizes of the K buffer (with its one-tile tail) and of V^T
@@ -292,10 +300,10 @@ hipError_t launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, 
     // workgroups (12 waves) share a CU (48 KB of LDS each).
     if (hd == 128)
         hipLaunchKernelGGL((attn_kernel<128, 32, 3, 3>), grid, dim3(256), 0, st, q, k, vt, o, Sq, Skv, n_keys, q_split,
-                           n_keys_lo, H, KV, scale_log2, (uint32_t)kb, (uint32_t)vb);
+                           n_keys_lo, block, H, KV, scale_log2, (uint32_t)kb, (uint32_t)vb);
     else if (hd == 64)
         hipLaunchKernelGGL((attn_kernel<64, 32, 3, 3>), grid, dim3(256), 0, st, q, k, vt, o, Sq, Skv, n_keys, q_split,
-                           n_keys_lo, H, KV, scale_log2, (uint32_t)kb, (uint32_t)vb);
+                           n_keys_lo, block, H, KV, scale_log2, (uint32_t)kb, (uint32_t)vb);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

@@ -9,9 +9,13 @@ namespace {
 // Ids outside [0, V) are clamped into range so that no read leaves the table,
 // and counted in *invalid together with [MASK] ids in the first mask_rows
 // positions of each row of S tokens (the prompt, which must hold real tokens).
+// With g, also the first block's input norm h[t] = bf16(x[t] / rms * g) of the
+// row in hand (the same arithmetic, in the same order, as the stand-alone
+// RMSNorm).
 __global__ void embed_kernel(const int32_t* __restrict__ tok, const bf16_t* __restrict__ emb,
                              float* __restrict__ x, int d, int V, int S, int mask_rows, int mask_id,
-                             int32_t* __restrict__ invalid) {
+                             int32_t* __restrict__ invalid, const bf16_t* __restrict__ g, bf16_t* __restrict__ h,
+                             float eps) {
     const int t = blockIdx.x;
     const int raw = tok[t];
     if (threadIdx.x == 0 && invalid && (raw < 0 || raw >= V || (t % S < mask_rows && raw == mask_id)))
@@ -19,6 +23,7 @@ __global__ void embed_kernel(const int32_t* __restrict__ tok, const bf16_t* __re
     const int id = min(max(raw, 0), V - 1);
     const bf16_t* src = emb + (int64_t)id * d;
     float* dst = x + (int64_t)t * d;
+    float ss = 0.f;
     for (int i = threadIdx.x * 8; i < d; i += blockDim.x * 8) {
         const u32x4 v = *reinterpret_cast<const u32x4*>(src + i);
         f32x4 lo, hi;
@@ -31,7 +36,10 @@ __global__ void embed_kernel(const int32_t* __restrict__ tok, const bf16_t* __re
         }
         *reinterpret_cast<f32x4*>(dst + i) = lo;
         *reinterpret_cast<f32x4*>(dst + i + 4) = hi;
+        ss += lo[0] * lo[0] + lo[1] * lo[1] + lo[2] * lo[2] + lo[3] * lo[3];
+        ss += hi[0] * hi[0] + hi[1] * hi[1] + hi[2] * hi[2] + hi[3] * hi[3];
     }
+    if (g) rms_store_row(dst, g, h + (int64_t)t * d, d, block_rms_scale(ss, d, eps));
 }
 
 // h = bf16(x / sqrt(mean(x^2) + eps) * g), fp32 math; one workgroup (256) per row.
@@ -61,35 +69,40 @@ __global__ void rmsnorm_draft_kernel(const float* __restrict__ x, const bf16_t* 
 }
 
 // Merge the per-vocabulary-tile partials of each row.  A workgroup handles 8
-// rows; each of the 32 thread groups of a row takes every 32nd tile (online
+// rows; each of the 128 thread groups of a row takes every 128th tile (online
 // merge in tile order; one read covers 8 consecutive rows = 128 contiguous
-// bytes), then the 32 group results are merged in group order through LDS.
-// The order is fixed, so results are deterministic; ties keep the lower
-// vocabulary id.
-__global__ __launch_bounds__(256) void lmhead_merge_kernel(const float4* __restrict__ part, int n_tiles, int R,
-                                                           int32_t* __restrict__ top1, float* __restrict__ conf,
-                                                           float* __restrict__ max_logit) {
-    __shared__ float4 red[32][8];
+// bytes), then the group results are merged as a tree through LDS.  The order
+// is fixed, so results are deterministic; ties keep the lower vocabulary id.
+// Each merge waits for two exponentials, so the chain is what counts: 1228
+// tiles over 32 groups, then one thread over the groups, took 21.2 us for 201
+// rows and 22.4 for 512.
+constexpr int kMergeGroups = 128;
+__global__ __launch_bounds__(8 * kMergeGroups) void lmhead_merge_kernel(const float4* __restrict__ part, int n_tiles, int R,
+                                                                        int32_t* __restrict__ top1, float* __restrict__ conf,
+                                                                        float* __restrict__ max_logit) {
+    __shared__ float4 red[kMergeGroups][8];
     const int rl = threadIdx.x & 7, split = threadIdx.x >> 3;
     const int r = blockIdx.x * 8 + rl;
     SoftmaxPartial acc{-INFINITY, 0x7fffffff, 0.f};
     if (r < R) {
-        for (int t = split; t < n_tiles; t += 32) {
+#pragma unroll 4
+        for (int t = split; t < n_tiles; t += kMergeGroups) {
             const float4 p = part[(int64_t)t * R + r];
             acc = sp_merge(acc, SoftmaxPartial{p.x, __float_as_int(p.y), p.z});
         }
     }
-    red[split][rl] = make_float4(acc.m, __int_as_float(acc.idx), acc.s, 0.f);
-    __syncthreads();
-    if (split == 0 && r < R) {
-        SoftmaxPartial a = acc;
-        for (int q = 1; q < 32; ++q) {
-            const float4 p = red[q][rl];
-            a = sp_merge(a, SoftmaxPartial{p.x, __float_as_int(p.y), p.z});
+    for (int n = kMergeGroups; n > 1; n >>= 1) {      // groups 0 .. n-1 hold results; the upper half hands over
+        if (split < n && split >= n / 2) red[split][rl] = make_float4(acc.m, __int_as_float(acc.idx), acc.s, 0.f);
+        __syncthreads();
+        if (split < n / 2) {
+            const float4 p = red[split + n / 2][rl];
+            acc = sp_merge(acc, SoftmaxPartial{p.x, __float_as_int(p.y), p.z});
         }
-        top1[r] = a.idx;
-        conf[r] = 1.f / a.s;
-        if (max_logit) max_logit[r] = a.m;
+    }
+    if (split == 0 && r < R) {
+        top1[r] = acc.idx;
+        conf[r] = 1.f / acc.s;
+        if (max_logit) max_logit[r] = acc.m;
     }
 }
 
@@ -272,19 +285,12 @@ __global__ void zero_i32_kernel(int32_t* __restrict__ p, int n) {
     if (i < n) p[i] = 0;
 }
 
-
-__global__ void vt_pad_zero_kernel(bf16_t* vt, int64_t n, int S, int pad, int stride) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t r = i / pad;
-    vt[r * stride + vt_pos(S + (int)(i - r * pad))] = 0;
-}
-
 }  // namespace
 
 void launch_embed(const int32_t* tokens, const bf16_t* emb, float* x, int T, int d, int V, int S, int mask_rows,
-                  int mask_id, int32_t* invalid, hipStream_t st) {
-    hipLaunchKernelGGL(embed_kernel, dim3(T), dim3(256), 0, st, tokens, emb, x, d, V, S, mask_rows, mask_id, invalid);
+                  int mask_id, int32_t* invalid, const bf16_t* g, bf16_t* h, float eps, hipStream_t st) {
+    hipLaunchKernelGGL(embed_kernel, dim3(T), dim3(256), 0, st, tokens, emb, x, d, V, S, mask_rows, mask_id, invalid, g,
+                       h, eps);
 }
 
 void launch_rmsnorm(const float* x, const bf16_t* g, bf16_t* h, int rows, int d, float eps,
@@ -299,7 +305,7 @@ void launch_rmsnorm_draft_rows(const float* x, const bf16_t* g, bf16_t* h, int B
 
 void launch_lmhead_merge(const float4* partials, int n_tiles, int R, int32_t* top1, float* conf,
                          float* max_logit, hipStream_t st) {
-    hipLaunchKernelGGL(lmhead_merge_kernel, dim3((R + 7) / 8), dim3(256), 0, st, partials,
+    hipLaunchKernelGGL(lmhead_merge_kernel, dim3((R + 7) / 8), dim3(8 * kMergeGroups), 0, st, partials,
                        n_tiles, R, top1, conf, max_logit);
 }
 
@@ -371,11 +377,4 @@ hipError_t launch_draft_select(int32_t* tokens, int B, int S, int c0, int L, con
 
 void launch_zero_i32(int32_t* p, int n, hipStream_t st) {
     hipLaunchKernelGGL(zero_i32_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n);
-}
-
-void launch_vt_pad_zero(bf16_t* vt, int64_t rows, int S, hipStream_t st) {
-    const int stride = vt_stride(S), pad = stride - S;
-    const int64_t n = rows * pad;
-    if (n == 0) return;
-    hipLaunchKernelGGL(vt_pad_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, vt, n, S, pad, stride);
 }

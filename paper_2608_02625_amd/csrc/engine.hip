@@ -317,6 +317,9 @@ struct Ctx {
     bool kv_only = false;               // stop after the last layer's K/V (cache commit)
     bool no_events = false;             // no profiling events (the entry point allocates nothing)
     int att_split = 0, att_keys_lo = 0;  // window rows below att_split see only att_keys_lo keys
+    int att_block = 0;                  // > 0: the rows from there on are blocks that see no later one
+    bool head_next = false;             // the head follows the last block
+    bool hfin_ready = false;            // hfin already holds the head's normalised rows
     float* dbg_router_logits = nullptr;  // test hook: router logits [T][E] of the layer run
     // Only the draft rows leave the last block (the head reads nothing else):
     // its MoE FFN then runs on the B*D draft rows alone.  Their K / V for the
@@ -437,20 +440,21 @@ GemmTile gate_up_tile(int64_t M, int64_t N, int64_t K) {
 }
 
 // Expert products of T tokens: what counts is the rows that an expert gets on
-// average.  gate/up + down, us, at d 2048, 64 experts of 1024, top 8: 12 rows
-// each 117 + 57 on 64x128, 144 + 63 on 128x128, 162 + 75 on the big tiles; 64
-// rows 137 + 68 / 144 + 68 / 169 + 81; 80 rows 147 + 77 / 145 + 70 / 168 + 81;
-// 128 rows - / 161 + 88 / 167 + 88; 158 rows - / 179 + 100 / 179 + 92.  An
-// expert with more than 64 rows takes its weights twice with 64-row tiles:
-// with 257 groups of 25 MB (d 4096) that costs more than the finer split gains
-// (64 rows: 1438 + 790 / 1244 + 702 / 1237 + 689), so from 40 rows on only
-// where the tiles are too few to even out (twice the resident workgroups).
+// average.  gate/up + down, us, at d 2048, 64 experts of 1024, top 8 (64x128 /
+// 128x128 / ping-pong tiles): 12 rows each 117 + 57 / 144 + 63 / 162 + 75; 64
+// rows 137 + 68 / 144 + 68 / 169 + 81; 80 rows 147 + 77 / 139 + 66 / 157 + 72;
+// 112 rows - / 140 + 70 / 165 + 78; 128 rows - / 165 + 86 / 168 + 82; 158 rows
+// - / 179 + 100 / 164 + 84.  An expert with more than 64 rows takes its weights
+// twice with 64-row tiles: with 257 groups of 25 MB (d 4096) that costs more
+// than the finer split gains (64 rows: 1438 + 790 / 1244 + 709 / 1230 + 672; 47
+// rows - / 1192 + 674 / 1205 + 646), so beyond 40 rows small tiles are for
+// models whose tiles are too few to even out otherwise.
 GemmTile expert_tile(const dlm_config& c, int64_t T) {
     const int64_t G = c.n_experts + c.n_shared_experts;
     const double rows = (double)T * c.top_k / c.n_experts;
     const int64_t narrow = G * ((2 * (int64_t)c.expert_ffn_dim + 127) / 128);
     if (rows <= 40 || (rows <= 72 && narrow <= 2048)) return {64, 128, 3};
-    if (rows <= (narrow <= 2048 ? 128 : 64)) return {128, 128, 3};
+    if (rows <= (narrow <= 2048 ? 120 : 48)) return {128, 128, 3};
     return {256, 256, 11};
 }
 
@@ -497,7 +501,7 @@ dlm_status run_layer(Ctx& x, int l) {
     {
         prof_begin(x, "attention");
         hipError_t e = launch_attention(q, k, v, attn, x.B, x.S, kvS, x.q0 + x.S, H, KV, hd, x.st, x.att_split,
-                                        x.att_keys_lo);
+                                        x.att_keys_lo, x.att_block);
         prof_end(x, "attention");
         if (e != hipSuccess) return fail(DLM_ERR_HIP, std::string("attention: ") + hipGetErrorString(e));
     }
@@ -606,23 +610,35 @@ dlm_status run_layer(Ctx& x, int l) {
         a.variant = et.variant;
         TRY(gemm(x, "gemm_expert_down", a, EPI_BF16, true, et.bm, et.bn, max_tiles));
     }
-    // The combine also normalises each finished row for the next block.
+    // The combine also normalises each finished row for the next block, or,
+    // where its rows are the head's in the head's order, for the head.
     const bool fuse = l + 1 < c.n_layers;
-    LAUNCH(x, "combine", launch_combine(xs, y, slot, wts, grp_off, Tf, kk, E, NS, d,
-                                        fuse ? x.wt(x.m->plan.layers[l + 1].g1) : nullptr, h, c.norm_eps, x.st,
+    x.hfin_ready = !fuse && x.head_next && (draft_ffn || x.P == 0);
+    const bf16_t* g_next = fuse ? x.wt(x.m->plan.layers[l + 1].g1) : x.hfin_ready ? x.wt(x.m->plan.gf) : nullptr;
+    LAUNCH(x, "combine", launch_combine(xs, y, slot, wts, grp_off, Tf, kk, E, NS, d, g_next,
+                                        fuse ? h : x.at<bf16_t>(x.w.hfin), c.norm_eps, x.st,
                                         draft_ffn ? x.S : 0, draft_ffn ? x.P : 0, draft_ffn ? x.D : 0));
     x.h_ready = fuse;
     return DLM_OK;
 }
 
-dlm_status run_prologue(Ctx& x, const int32_t* tokens) {
+// Token rows into the residual stream and, normalised, into the first block's input.
+void run_embed(Ctx& x, const int32_t* tokens, int mask_rows, int32_t* invalid) {
     const dlm_config& c = x.c;
-    LAUNCH(x, "rope_table", launch_rope_table(x.at<float2>(x.w.rope), x.S, c.head_dim / 2, (double)c.rope_theta, x.P,
-                                              x.pos_shift, x.st));
-    LAUNCH(x, "vt_pad_zero", launch_vt_pad_zero(x.at<bf16_t>(x.w.v), (int64_t)x.B * c.n_kv_heads * c.head_dim, x.S, x.st));
-    if (tokens)
-        LAUNCH(x, "embed", launch_embed(tokens, x.wt(x.m->plan.emb), x.at<float>(x.w.x), x.T, c.d_model, c.vocab, x.S,
-                                        x.P, c.mask_id, x.at<int32_t>(x.w.counters) + CNT_INVALID, x.st));
+    x.h_ready = c.n_layers > 0;
+    LAUNCH(x, "embed", launch_embed(tokens, x.wt(x.m->plan.emb), x.at<float>(x.w.x), x.T, c.d_model, c.vocab, x.S,
+                                    mask_rows, c.mask_id, invalid,
+                                    x.h_ready ? x.wt(x.m->plan.layers[0].g1) : nullptr, x.at<bf16_t>(x.w.h), c.norm_eps,
+                                    x.st));
+}
+
+dlm_status run_prologue(Ctx& x, const int32_t* tokens, bool clear_counters) {
+    const dlm_config& c = x.c;
+    int32_t* counters = x.at<int32_t>(x.w.counters);
+    LAUNCH(x, "pass_setup", launch_pass_setup(x.at<float2>(x.w.rope), x.S, c.head_dim / 2, (double)c.rope_theta, x.P,
+                                              x.pos_shift, x.at<bf16_t>(x.w.v), (int64_t)x.B * c.n_kv_heads * c.head_dim,
+                                              counters, clear_counters ? CNT_WORDS : 0, x.st));
+    if (tokens) run_embed(x, tokens, x.P, counters + CNT_INVALID);
     return DLM_OK;
 }
 
@@ -630,8 +646,9 @@ dlm_status run_prologue(Ctx& x, const int32_t* tokens) {
 dlm_status run_head(Ctx& x, int32_t* top1, float* conf, float* maxlogit, float* logits_out) {
     const dlm_config& c = x.c;
     bf16_t* hfin = x.at<bf16_t>(x.w.hfin);
-    LAUNCH(x, "rmsnorm_final", launch_rmsnorm_draft_rows(x.at<float>(x.w.x), x.wt(x.m->plan.gf), hfin, x.B,
-                                                         x.S, x.P, x.D, c.d_model, c.norm_eps, x.st));
+    if (!x.hfin_ready)
+        LAUNCH(x, "rmsnorm_final", launch_rmsnorm_draft_rows(x.at<float>(x.w.x), x.wt(x.m->plan.gf), hfin, x.B,
+                                                             x.S, x.P, x.D, c.d_model, c.norm_eps, x.st));
     GemmArgs a = gemm_args(x.wt(x.m->plan.lm), c.d_model, hfin, c.d_model, c.vocab, x.R, c.d_model);
     a.partials = x.at<float4>(x.w.partials);
     a.group_m = 4;
@@ -671,9 +688,9 @@ dlm_status step_impl(Ctx& x, int32_t* tokens, const dlm_edit_rule& rule, int32_t
     const dlm_config& c = x.c;
     int32_t* counters = x.at<int32_t>(x.w.counters);
     int32_t* eos = counters + CNT_EOS;
-    LAUNCH(x, "zero", launch_zero_i32(counters, CNT_WORDS, x.st));
-    TRY(run_prologue(x, tokens));
+    TRY(run_prologue(x, tokens, true));
     x.draft_rows_last_ffn = true;
+    x.head_next = true;
     for (int l = 0; l < c.n_layers; ++l) TRY(run_layer(x, l));
     TRY(run_head(x, x.at<int32_t>(x.w.top1), x.at<float>(x.w.conf), x.at<float>(x.w.maxlogit), nullptr));
     LAUNCH(x, "edit", launch_edit(tokens, x.B, x.S, x.P, x.D, x.at<int32_t>(x.w.top1), x.at<float>(x.w.conf),
@@ -761,43 +778,66 @@ struct Drafter {
     }
     int32_t* counters() const { return reinterpret_cast<int32_t*>(ws + p.w.counters); }
 
-    // Forward of one window of the token state: all layers' K/V of its rows go
-    // into the caches; with head, also the top-1 / confidence of its rows from
-    // row `lead` on.  The first `lead` rows are a finished block carried along
-    // to commit its K/V: they see keys only up to their own end.
-    dlm_status run(const int32_t* tokens, int c0, int L, bool head, int lead = 0) const {
+    // Forward of the window [c0, c0 + L) of the token state, which starts at 0
+    // or at a block and ends with a block or the prompt: all layers' K/V of its
+    // rows go into the caches, every row seeing the keys up to its own block's
+    // end (the prompt: its own).  With head_rows > 0, also the top-1 /
+    // confidence of its last head_rows rows; the last block's FFN then runs on
+    // those alone.
+    dlm_status run(const int32_t* tokens, int c0, int L, int head_rows) const {
         Ctx x = window(c0, L);
         const dlm_config& c = m->cfg;
-        x.kv_only = !head;
-        if (lead) {
-            x.P = lead;
-            x.D = L - lead;
-            x.R = B * (L - lead);
-            x.att_split = lead;
-            x.att_keys_lo = c0 + lead;
+        x.kv_only = head_rows == 0;
+        if (head_rows) {
+            x.P = L - head_rows;
+            x.D = head_rows;
+            x.R = B * head_rows;
+            x.draft_rows_last_ffn = x.head_next = true;
         }
+        const int prompt_rows = std::max(0, std::min(P - c0, L));
+        if (prompt_rows > 0 && prompt_rows < L) {
+            x.att_split = prompt_rows;
+            x.att_keys_lo = P;
+        }
+        if (L - prompt_rows > blk) x.att_block = blk;
         int32_t* wtok = x.at<int32_t>(p.wtok);
         LAUNCH(x, "window_gather", launch_window_gather(tokens, wtok, B, S, c0, L, st));
-        // a window inside the prompt must hold no [MASK] id; every id must lie in [0, vocab)
-        LAUNCH(x, "embed", launch_embed(wtok, x.wt(m->plan.emb), x.at<float>(p.w.x), x.T, c.d_model, c.vocab, L,
-                                        c0 + L <= P ? L : 0, c.mask_id, counters() + CNT_INVALID, st));
+        // the prompt must hold no [MASK] id; every id must lie in [0, vocab)
+        run_embed(x, wtok, prompt_rows, counters() + CNT_INVALID);
         for (int l = 0; l < c.n_layers; ++l) TRY(run_layer(x, l));
-        if (head) TRY(run_head(x, x.at<int32_t>(p.w.top1), x.at<float>(p.w.conf), x.at<float>(p.w.maxlogit), nullptr));
+        if (head_rows)
+            TRY(run_head(x, x.at<int32_t>(p.w.top1), x.at<float>(p.w.conf), x.at<float>(p.w.maxlogit), nullptr));
         HIP_TRY(hipGetLastError());
         return DLM_OK;
     }
 
-    // Fresh caches (zero, so the attention's tile reads past the visible keys
-    // meet finite values), the RoPE table, and the prompt's K/V: the prompt
-    // attends to itself only.
-    dlm_status begin(const int32_t* tokens) const {
+    // The RoPE table and caches whose unwritten positions can be read: the
+    // attention reads whole 32-key tiles past the visible keys and masks the
+    // scores there, whatever K holds, but V must be finite.  Positions past the
+    // end of the prompt or a block are read before they are written only where
+    // those ends are not multiples of 32.
+    dlm_status begin() const {
         const dlm_config& c = m->cfg;
         Ctx x = window(0, 1);
-        launch_fill_bf16(x.kc, (uint64_t)c.n_layers * p.kc_layer + 64 * c.head_dim, 0, st);
-        launch_fill_bf16(x.vc, (uint64_t)c.n_layers * p.vc_layer, 0, st);
+        if (P % 32 || blk % 32 || S % 32) launch_fill_bf16(x.vc, (uint64_t)c.n_layers * p.vc_layer, 0, st);
         launch_rope_table(x.at<float2>(p.rope), S, c.head_dim / 2, (double)c.rope_theta, S, 0, st);
         HIP_TRY(hipGetLastError());
-        if (P > 0) TRY(run(tokens, 0, P, false));
+        return DLM_OK;
+    }
+
+    // Forward of everything up to the end of block k, the head on block k, in
+    // as few windows as the window buffers allow: the weights are read once per
+    // window, and a window of one block leaves most of the chip idle.
+    dlm_status run_up_to(const int32_t* tokens, int k) const {
+        const int end = block_start(k) + block_rows(k);
+        int c0 = 0;
+        while (c0 < end) {
+            // the longest run of whole segments from c0 that fits
+            int c1 = c0 < P ? P : std::min(c0 + blk, end);
+            while (c1 < end && std::min(c1 + blk, end) - c0 <= p.rows) c1 = std::min(c1 + blk, end);
+            TRY(run(tokens, c0, c1 - c0, c1 == end ? block_rows(k) : 0));
+            c0 = c1;
+        }
         return DLM_OK;
     }
 
@@ -806,15 +846,18 @@ struct Drafter {
 
     // One denoising step on block k: forward of the block's window, then the
     // unmasking.  With with_prev, the window also carries block k-1 (finished,
-    // its K/V not yet in the caches), which commits it in the same pass.
+    // its K/V not yet in the caches), which commits it in the same pass; with
+    // from_start everything before the block is computed first.
     // counters: [0] unmasked, [2] masked left in the block, [3] = 1.
     dlm_status step(int32_t* tokens, int k, float tau, int steps_left, int32_t* top1_out, float* conf_out,
-                    bool with_prev = false) const {
+                    bool with_prev = false, bool from_start = false) const {
         const int c0 = block_start(k), L = block_rows(k);
-        if (with_prev)
-            TRY(run(tokens, c0 - blk, blk + L, true, blk));
+        if (from_start)
+            TRY(run_up_to(tokens, k));
+        else if (with_prev)
+            TRY(run(tokens, c0 - blk, blk + L, L));
         else
-            TRY(run(tokens, c0, L, true));
+            TRY(run(tokens, c0, L, L));
         Ctx x = window(c0, L);
         launch_zero_i32(counters(), 4, st);
         prof_begin(x, "draft_select");
@@ -1182,9 +1225,8 @@ dlm_status dlm_draft_step(dlm_model* m, int32_t batch, int32_t prompt_len, int32
         const Drafter dr{m, (char*)d_workspace, p, (hipStream_t)hip_stream, batch, prompt_len, draft_len,
                          prompt_len + draft_len, block_len};
         launch_zero_i32(dr.counters(), CNT_WORDS, dr.st);
-        TRY(dr.begin(d_tokens));
-        for (int j = 0; j < block_index; ++j) TRY(dr.run(d_tokens, dr.block_start(j), block_len, false));
-        TRY(dr.step(d_tokens, block_index, threshold, steps_left, d_top1, d_conf));
+        TRY(dr.begin());
+        TRY(dr.step(d_tokens, block_index, threshold, steps_left, d_top1, d_conf, false, true));
         if (d_stats) HIP_TRY(hipMemcpyAsync(d_stats, dr.counters(), sizeof(dlm_stats), hipMemcpyDeviceToDevice, dr.st));
         if (d_max_logit)
             HIP_TRY(hipMemcpyAsync(d_max_logit, dr.ws + p.w.maxlogit, (size_t)batch * dr.block_rows(block_index) * 4,
@@ -1211,7 +1253,8 @@ dlm_status dlm_draft(dlm_model* m, int32_t batch, int32_t prompt_len, int32_t dr
         launch_zero_i32(dr.counters(), CNT_WORDS, dr.st);
         launch_draft_init(d_prompt, tokens, batch, prompt_len, S, m->cfg.vocab, m->cfg.mask_id, dr.counters(), dr.st);
         HIP_TRY(hipGetLastError());
-        TRY(dr.begin(tokens));
+        TRY(dr.begin());
+        if (prompt_len > 0) TRY(dr.run(tokens, 0, prompt_len, 0));
         const int n_blocks = (draft_len + block_len - 1) / block_len;
         dlm_stats tot{0, 0, 0, 0, 0};
         for (int k = 0; k < n_blocks; ++k) {
@@ -1299,7 +1342,7 @@ dlm_status dlm_debug_forward(dlm_model* m, int32_t batch, int32_t prompt_len, in
         TRY(check_common(m, batch, prompt_len, draft_len, d_workspace, workspace_bytes, &w));
         if (!d_tokens) return fail(DLM_ERR_INVALID_ARG, "tokens is NULL");
         Ctx x = ctx_for(m, batch, prompt_len, draft_len, d_workspace, w, hip_stream);
-        TRY(run_prologue(x, d_tokens));
+        TRY(run_prologue(x, d_tokens, false));
         const size_t route_words = (size_t)x.T * m->cfg.top_k;
         for (int l = 0; l < m->cfg.n_layers; ++l) {
             if (d_router_logits && m->cfg.n_experts > 0)
@@ -1337,7 +1380,7 @@ dlm_status dlm_debug_layer(dlm_model* m, int32_t layer, int32_t batch, int32_t s
         if (m->cfg.n_experts > 0) x.dbg_router_logits = d_router_logits;
         const size_t bytes = (size_t)x.T * m->cfg.d_model * 4;
         HIP_TRY(hipMemcpyAsync(x.at<float>(w.x), d_x_in, bytes, hipMemcpyDeviceToDevice, x.st));
-        TRY(run_prologue(x, nullptr));
+        TRY(run_prologue(x, nullptr, false));
         TRY(run_layer(x, layer));
         HIP_TRY(hipMemcpyAsync(d_x_out, x.at<float>(w.x), bytes, hipMemcpyDeviceToDevice, x.st));
         if (d_route_ids && m->cfg.n_experts > 0)

@@ -85,15 +85,36 @@ __global__ void fill_bf16_kernel(bf16_t* __restrict__ dst, uint64_t n, bf16_t v)
 // evaluated in double and rounded to float.  Row s holds position s for the
 // first P rows and s + shift after them (a draft span refined on its own keeps
 // its positions in the full sequence).
-__global__ void rope_table_kernel(float2* __restrict__ tab, int S, int half, double theta, int P, int shift) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= S * half) return;
+__device__ __forceinline__ void rope_entry(float2* __restrict__ tab, int idx, int half, double theta, int P, int shift) {
     const int row = idx / half, i = idx % half;
     const int pos = row < P ? row : row + shift;
     const double inv = pow(theta, -2.0 * (double)i / (double)(2 * half));
     double s, c;
     sincos((double)pos * inv, &s, &c);
     tab[idx] = make_float2((float)c, (float)s);
+}
+
+__global__ void rope_table_kernel(float2* __restrict__ tab, int S, int half, double theta, int P, int shift) {
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx < S * half) rope_entry(tab, idx, half, theta, P, shift);
+}
+
+// What a pass needs before its first block, in one launch (as three, 2 to 4 us
+// each with nothing to do but start and end): the RoPE table, zeros in the V^T
+// positions of keys S .. S64-1, and cleared counters.
+__global__ void pass_setup_kernel(float2* __restrict__ tab, int S, int half, double theta, int P, int shift,
+                                  int rope_blocks, bf16_t* __restrict__ vt, int64_t vt_n, int pad, int stride,
+                                  int32_t* __restrict__ counters, int n_counters) {
+    if (blockIdx.x == 0 && threadIdx.x < n_counters) counters[threadIdx.x] = 0;
+    if ((int)blockIdx.x < rope_blocks) {
+        const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+        if (idx < S * half) rope_entry(tab, idx, half, theta, P, shift);
+        return;
+    }
+    const int64_t i = (int64_t)(blockIdx.x - rope_blocks) * blockDim.x + threadIdx.x;
+    if (i >= vt_n) return;
+    const int64_t r = i / pad;
+    vt[r * stride + vt_pos(S + (int)(i - r * pad))] = 0;
 }
 
 }  // namespace
@@ -113,4 +134,13 @@ void launch_fill_bf16(bf16_t* dst, uint64_t n, bf16_t v, hipStream_t st) {
 void launch_rope_table(float2* tab, int S, int half, double theta, int P, int shift, hipStream_t st) {
     const int n = S * half;
     hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, tab, S, half, theta, P, shift);
+}
+
+void launch_pass_setup(float2* tab, int S, int half, double theta, int P, int shift, bf16_t* vt, int64_t vt_rows,
+                       int32_t* counters, int n_counters, hipStream_t st) {
+    const int stride = vt_stride(S), pad = stride - S;
+    const int64_t vt_n = vt_rows * pad;
+    const int rope_blocks = (S * half + 255) / 256;
+    hipLaunchKernelGGL(pass_setup_kernel, dim3((unsigned)(rope_blocks + (vt_n + 255) / 256)), dim3(256), 0, st, tab, S,
+                       half, theta, P, shift, rope_blocks, vt, vt_n, pad, stride, counters, n_counters);
 }

@@ -12,6 +12,10 @@ void launch_init_weights(bf16_t* dst, uint64_t n_phys, uint32_t cols, uint32_t t
 void launch_fill_bf16(bf16_t* dst, uint64_t n, bf16_t v, hipStream_t st);
 // RoPE (cos, sin) table [S][half]; rows >= P take position row + shift.
 void launch_rope_table(float2* tab, int S, int half, double theta, int P, int shift, hipStream_t st);
+// The same table, zeros in the V^T positions of keys S .. S64-1 of vt_rows rows
+// (vt_stride), and n_counters <= 256 cleared words.
+void launch_pass_setup(float2* tab, int S, int half, double theta, int P, int shift, bf16_t* vt, int64_t vt_rows,
+                       int32_t* counters, int n_counters, hipStream_t st);
 
 // V is kept transposed for attention: V^T [B][KV][hd][S64], S64 = S rounded up
 // to the 64-key attention tile.  Inside each aligned group of 16 keys the keys
@@ -80,10 +84,13 @@ hipError_t launch_gemm(const GemmArgs& a, int epi, bool grouped, int bm, int bn,
 // Draft windows: Q holds Sq rows per sequence, K and V^T hold Skv rows per
 // sequence of which the first n_keys are visible (n_keys <= Skv); O [B*Sq][H*hd].
 // With q_split > 0 the first q_split query rows see only the first n_keys_lo
-// keys (1 <= n_keys_lo <= n_keys).
+// keys (1 <= n_keys_lo <= n_keys).  With block > 0 the rows from q_split on are
+// blocks of that many positions, each seeing the keys up to its own end: row
+// q_split + i the first n_keys - (Sq - q_split) + (i / block + 1) * block of
+// them, at most n_keys (0: all n_keys).
 hipError_t launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, int B,
                             int Sq, int Skv, int n_keys, int H, int KV, int hd, hipStream_t st, int q_split = 0,
-                            int n_keys_lo = 0);
+                            int n_keys_lo = 0, int block = 0);
 
 // Per-pass counters in the workspace (int32 words; the first five are the
 // dlm_stats layout).
@@ -100,9 +107,10 @@ enum PassCounter {
 // ----------------------------------------------------------------- elementwise.hip
 // x[t] = E[tokens[t]] for T = rows of S tokens.  Ids outside [0, V) are
 // clamped for the read and counted in *invalid, as are [MASK] ids among the
-// first mask_rows tokens of each row of S (the prompt).
+// first mask_rows tokens of each row of S (the prompt).  With g != nullptr, also
+// writes h = RMSNorm(x) * g (bf16) for the first block.
 void launch_embed(const int32_t* tokens, const bf16_t* emb, float* x, int T, int d, int V, int S, int mask_rows,
-                  int mask_id, int32_t* invalid, hipStream_t st);
+                  int mask_id, int32_t* invalid, const bf16_t* g, bf16_t* h, float eps, hipStream_t st);
 void launch_rmsnorm(const float* x, const bf16_t* g, bf16_t* h, int rows, int d, float eps,
                     hipStream_t st);
 // rows (b, P + i) for i < D of a [B][S] stream -> h [B*D][d]
@@ -142,9 +150,6 @@ void launch_window_gather(const int32_t* tokens, int32_t* out, int B, int S, int
 hipError_t launch_draft_select(int32_t* tokens, int B, int S, int c0, int L, const int32_t* top1, const float* conf,
                                float tau, int steps_left, int mask_id, int32_t* counters, int32_t* out_top1,
                                float* out_conf, hipStream_t st);
-// Zero the V^T positions of keys S .. S64-1 in every one of `rows` rows.
-void launch_vt_pad_zero(bf16_t* vt, int64_t rows, int S, hipStream_t st);
-
 // ----------------------------------------------------------------- moe.hip
 // Router logits of T tokens (h [T][d] bf16, Wr [E][d] bf16, E <= 256), as n_split
 // partial sums parts [n_split][T][E] (1, 2, 4 or 8, at most router_parts(d));

@@ -425,3 +425,31 @@ def test_draft_random_dense_shapes(i):
            f"V{s.vocab} B{B} P{P} D{D} b{b} s{steps} t{tau}")
     checked, bs = _trajectory(R, W, s, prompt, D, b, steps, tau, MARGIN * s.lm_head_scale, tag)
     assert len(bs) == -(-D // b) and checked > 0
+
+
+@pytest.mark.parametrize("P,blk,D", [(32, 32, 96), (0, 64, 128), (64, 32, 64), (40, 32, 96), (32, 24, 72)])
+def test_drafting_reads_no_unwritten_cache(P, blk, D):
+    """Caches are cleared only where block ends are not multiples of the
+    attention's 32-key tile; a workspace full of NaN patterns must not show."""
+    need_gpu()
+    import torch
+    from paper_2608_02625_amd import Refiner
+    shape = WORKLOADS["tiny"].model.replace(lm_head_scale=10.0)
+    R = Refiner(shape.as_dict(), 4)
+    g = torch.Generator().manual_seed(P + blk)
+    tok = torch.randint(0, shape.vocab - 1, (2, P + D), generator=g, dtype=torch.int32)
+    tok[:, P + D - blk:] = shape.mask_id
+    out = []
+    for fill in (0, 255):
+        R.draft_workspace(2, P, D, blk).fill_(fill)
+        t = tok.cuda()
+        t1 = torch.empty(2, blk, dtype=torch.int32, device="cuda")
+        cf = torch.empty(2, blk, dtype=torch.float32, device="cuda")
+        R.draft_step(t, P, blk, D // blk - 1, 2, 0.5, top1=t1, conf=cf)
+        R.draft_workspace(2, P, D, blk).fill_(fill)
+        d, st = R.draft(t[:, :P].contiguous(), D, blk, 3, 0.4)
+        torch.cuda.synchronize()
+        out.append((t.cpu(), t1.cpu(), cf.cpu(), d.cpu()))
+        assert torch.isfinite(cf).all()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
