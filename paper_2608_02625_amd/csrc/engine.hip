@@ -207,7 +207,7 @@ WeightPlan plan_weights(const dlm_config& c) {
 // Workspace carve-up for one (B, P, D).
 struct Workspace {
     size_t total = 0;
-    size_t x, h, q, k, v, attn, rope, hf, ids, wts, grp_off,
+    size_t x, h, q, k, v, attn, rope, hf, ids, wts, grp_off, tile_tab,
         n_tiles, slot, a_rows, ecount, hexp, y, hfin, partials, top1, conf, maxlogit, counters, tokens;
     int rows_total = 0, n_vtiles = 0;
 };
@@ -238,6 +238,7 @@ Workspace plan_workspace(const dlm_config& c, int B, int P, int D) {
         w.ids = add(T * k * 4);
         w.wts = add(T * k * 4);
         w.grp_off = add((G + 1) * 4);
+        w.tile_tab = add((int64_t)((w.rows_total + 255) / 256 + G) * 8);   // of 256-row tiles
         w.n_tiles = add(4);
         w.slot = add(T * k * 4);
         w.a_rows = add((int64_t)w.rows_total * 4);
@@ -541,13 +542,15 @@ dlm_status run_layer(Ctx& x, int l) {
     int32_t* ids = x.at<int32_t>(x.w.ids);
     float* wts = x.at<float>(x.w.wts);
     int32_t* grp_off = x.at<int32_t>(x.w.grp_off);
-    // The tile table lies in the attention output's buffer, which is free from
-    // the O projection to the next block's attention: at most one 8-byte entry
-    // per row of the experts (9 per token) against 256 bytes or more per token.
-    int2* tile_tab = x.at<int2>(x.w.attn);
     const GemmTile et = expert_tile(c, Tf);
     const int rows_total = Tf * (kk + NS);
     const int max_tiles = std::min(rows_total, rows_total / et.bm + E + NS);
+    // The table of smaller tiles is longer than the one of 256-row tiles, and
+    // lies in the attention output's buffer, which is free from the O projection
+    // to the next block's attention: at most one 8-byte entry per row of the
+    // experts (9 per token) against 256 bytes or more per token.
+    const bool tab_in_attn = et.bm < 256;
+    int2* tile_tab = x.at<int2>(tab_in_attn ? x.w.attn : x.w.tile_tab);
     int32_t* n_tiles = x.at<int32_t>(x.w.n_tiles);
     int32_t* slot = x.at<int32_t>(x.w.slot);
     int32_t* a_rows = x.at<int32_t>(x.w.a_rows);
@@ -564,9 +567,9 @@ dlm_status run_layer(Ctx& x, int l) {
         float* parts = x.at<float>(in_y ? x.w.hexp : x.w.q);
         const int n_split = router_splits(Tf, d, E, in_y ? cap_y : (int64_t)Tf * E * 4);
         // Selection counts of groups of 8 tokens (see router_group_tokens) lie
-        // behind the tile table where that buffer holds both; else groups of
-        // 32, whose counts have a place of their own.
-        const size_t tab_bytes = align_up((size_t)max_tiles * 8);
+        // in the attention output's buffer too where it holds both; else groups
+        // of 32, whose counts have a place of their own.
+        const size_t tab_bytes = tab_in_attn ? align_up((size_t)max_tiles * 8) : 0;
         int group = router_group_tokens(Tf, E, 8);
         if (in_y && tab_bytes + (size_t)E * ((Tf + group - 1) / group) * 4 <= (size_t)Tf * H * hd * 2)
             wg_counts = x.at<int32_t>(x.w.attn + tab_bytes);
