@@ -225,16 +225,23 @@ Workspace plan_workspace(const dlm_config& c, int B, int P, int D) {
     };
     w.x = add(T * d * 4);
     w.h = add(T * d * 2);
+    w.v = add((int64_t)B * c.n_kv_heads * hd * vt_stride((int)S) * 2);   // V^T, rows padded to tiles
+    // Q, K, the attention output and the expert buffers follow each other: the
+    // router's partial logits may run from Q into them (run_layer).  V^T must
+    // stay outside: its positions of keys S .. S64-1 are zero for a whole pass.
     w.q = add((int64_t)B * c.n_heads * S * hd * 2);
     w.k = add(((int64_t)B * c.n_kv_heads * S + 64) * hd * 2);         // + one 64-key tile of tail
-    w.v = add((int64_t)B * c.n_kv_heads * hd * vt_stride((int)S) * 2);   // V^T, rows padded to tiles
     w.attn = add(T * c.n_heads * hd * 2);
+    if (c.n_experts > 0) {
+        w.rows_total = (int)(T * c.top_k + T * c.n_shared_experts);
+        w.hexp = add((int64_t)w.rows_total * c.expert_ffn_dim * 2);
+        w.y = add((int64_t)w.rows_total * d * 2);
+    }
     w.rope = add(S * (hd / 2) * 8);
     if (c.n_experts == 0) {
         w.hf = add(T * c.ffn_dim * 2);
     } else {
         const int E = c.n_experts, k = c.top_k, G = E + c.n_shared_experts;
-        w.rows_total = (int)(T * k + T * c.n_shared_experts);
         w.ids = add(T * k * 4);
         w.wts = add(T * k * 4);
         w.grp_off = add((G + 1) * 4);
@@ -243,8 +250,6 @@ Workspace plan_workspace(const dlm_config& c, int B, int P, int D) {
         w.slot = add(T * k * 4);
         w.a_rows = add((int64_t)w.rows_total * 4);
         w.ecount = add((T + 31) / 32 * E * 4);           // per expert and router group (of 32 tokens) counts
-        w.hexp = add((int64_t)w.rows_total * c.expert_ffn_dim * 2);
-        w.y = add((int64_t)w.rows_total * d * 2);
     }
     w.n_vtiles = 2 * ((c.vocab + kHeadBM - 1) / kHeadBM);   // LM-head partials per half tile
     w.hfin = add(R * d * 2);
@@ -560,8 +565,10 @@ dlm_status run_layer(Ctx& x, int l) {
     {
         // The partial logits go where the expert products will write (nothing
         // there is live yet), or, where a logit row is longer than an expert
-        // row pair, into Q, K, V^T and the attention output: 256 bytes or more
-        // each per token, a row of 256 logits.
+        // row pair, from Q on through K and the attention output into those
+        // buffers: 256 bytes or more per token for each of Q, K, the attention
+        // output and an expert row, 128 or more for its hidden row; a row of
+        // 256 logits is 1024.  V^T is not among them (plan_workspace).
         const int64_t cap_y = (int64_t)(x.w.y - x.w.hexp) + (int64_t)rows_total * d * 2;
         const bool in_y = cap_y >= (int64_t)Tf * E * 4;
         float* parts = x.at<float>(in_y ? x.w.hexp : x.w.q);

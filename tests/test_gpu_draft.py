@@ -431,10 +431,25 @@ def test_draft_random_dense_shapes(i):
 def test_drafting_reads_no_unwritten_cache(P, blk, D):
     """Caches are cleared only where block ends are not multiples of the
     attention's 32-key tile; a workspace full of NaN patterns must not show."""
+    _reads_no_unwritten(WORKLOADS["tiny"].model.replace(lm_head_scale=10.0), P, blk, D)
+
+
+@pytest.mark.parametrize("P,blk,D", [(32, 32, 96), (0, 64, 128), (40, 32, 96), (32, 24, 72)])
+@pytest.mark.parametrize("over", [
+    dict(d_model=256, n_heads=4, n_kv_heads=2, head_dim=64, n_experts=24, top_k=3, expert_ffn_dim=192, n_shared_experts=1),
+    # logit rows longer than an expert row pair
+    dict(d_model=128, n_heads=2, n_kv_heads=2, head_dim=64, n_experts=256, top_k=1, expert_ffn_dim=64, n_shared_experts=0),
+])
+def test_moe_drafting_reads_no_unwritten_cache(over, P, blk, D):
+    """The same over three expert blocks, whose router and dispatch keep their
+    tables in buffers that the next block's attention uses."""
+    _reads_no_unwritten(WORKLOADS["tiny"].model.replace(n_layers=3, ffn_dim=0, lm_head_scale=10.0, **over), P, blk, D)
+
+
+def _reads_no_unwritten(shape, P, blk, D):
     need_gpu()
     import torch
     from paper_2608_02625_amd import Refiner
-    shape = WORKLOADS["tiny"].model.replace(lm_head_scale=10.0)
     R = Refiner(shape.as_dict(), 4)
     g = torch.Generator().manual_seed(P + blk)
     tok = torch.randint(0, shape.vocab - 1, (2, P + D), generator=g, dtype=torch.int32)

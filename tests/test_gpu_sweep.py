@@ -70,7 +70,7 @@ def test_random_larger_shape(i):
     _check(*_case(i, big=True), f"sweep big {i}")
 
 
-def _check(shape, B, P, D, seed, tag):
+def _check(shape, B, P, D, seed, tag, workspace_fill=None):
     need_gpu()
     import torch
     import oracle
@@ -82,6 +82,8 @@ def _check(shape, B, P, D, seed, tag):
     toks[:, P + 1::4] = shape.mask_id
     T, d = toks.size, shape.d_model
     g = torch.tensor(toks, device="cuda")
+    if workspace_fill is not None:
+        R.workspace(B, P, D).fill_(workspace_fill)
     out = R.debug_forward(g, P, want_routes=True)
     x_ref, infos, _ = oracle.forward(W, toks, collect=True)
     alike = np.ones(T, dtype=bool)
@@ -93,6 +95,7 @@ def _check(shape, B, P, D, seed, tag):
         o_z = np.stack([inf["router_logits"].reshape(T, E) for inf in infos])
         o_ids = np.stack([inf["route_ids"].reshape(T, k) for inf in infos])
         gaps = np.stack([inf["route_gap"].reshape(T) for inf in infos])
+        assert np.isfinite(g_z).all()                          # a NaN would pass every comparison below
         err = np.max(np.abs(g_z - o_z), -1)
         assert np.array_equal(np.argsort(-g_z, axis=-1, kind="stable")[..., :k], g_ids)
         differs = np.any(np.sort(g_ids, -1) != np.sort(o_ids, -1), -1)
@@ -101,6 +104,7 @@ def _check(shape, B, P, D, seed, tag):
         alike = ~np.any(differs, 0)
         n_flip = int((~alike).sum())
     hid = out["hidden"].cpu().numpy()
+    assert np.isfinite(hid).all()
     ref = x_ref.reshape(-1, d)
     eh = max_abs_rel(hid[alike], ref[alike]) if alike.any() else 0.0
     red = oracle.lm_head_reduce(W, x_ref[:, P:].reshape(-1, d))
@@ -109,8 +113,11 @@ def _check(shape, B, P, D, seed, tag):
     # the step (last-block MoE FFN on the draft rows) against the full forward
     t1 = torch.empty(B * D, dtype=torch.int32, device="cuda")
     cf = torch.empty(B * D, dtype=torch.float32, device="cuda")
+    if workspace_fill is not None:
+        R.workspace(B, P, D).fill_(workspace_fill)
     R.refine_step(g.clone(), P, 1.5, top1=t1, conf=cf)
     torch.cuda.synchronize()
+    assert bool(((cf > 0) & (cf <= 1)).all())
     same = bool(torch.equal(t1, out["top1"]) and torch.equal(cf, out["conf"]))
     log(f"[{tag}] L{shape.n_layers} d{d} H{shape.n_heads}/{shape.n_kv_heads}x{shape.head_dim} "
         f"E{shape.n_experts}k{shape.top_k}F{shape.expert_ffn_dim or shape.ffn_dim}s{shape.n_shared_experts} "

@@ -70,6 +70,19 @@ def test_router_against_the_oracle(over, B, P, D):
     _check(MODELS["tiny"].replace(n_layers=1, ffn_dim=0, vocab=500, **over), B, P, D, 91, f"router {over['n_experts']}")
 
 
+@pytest.mark.parametrize("experts,blocks,B,P,D", [
+    (256, 2, 2, 3, 30), (256, 3, 1, 0, 37), (200, 2, 2, 7, 30), (200, 3, 3, 60, 70), (129, 2, 1, 1, 96),
+])
+def test_narrow_experts_over_several_blocks(experts, blocks, B, P, D):
+    """Logit rows longer than an expert row pair, in a model of several blocks
+    with sequences that end inside a 32-key tile: what the router leaves behind
+    must not show in the next block's attention, whatever the workspace held."""
+    shape = MODELS["tiny"].replace(n_layers=blocks, d_model=128, n_heads=2, n_kv_heads=2, head_dim=64, ffn_dim=0,
+                                   n_experts=experts, top_k=1, expert_ffn_dim=64, n_shared_experts=0, vocab=500)
+    assert (P + D) % 32 != 0 and 2 * (shape.expert_ffn_dim + shape.d_model) < 4 * experts
+    _check(shape, B, P, D, 17, f"narrow {experts}", workspace_fill=255)
+
+
 @pytest.mark.parametrize("experts,shared", [(3, 0), (8, 1)])
 def test_rows_of_every_expert_tile_height(experts, shared):
     """With top-k = E every expert gets every row: the row counts walk over the
