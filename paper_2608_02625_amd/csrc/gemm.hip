@@ -25,6 +25,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "tiling.h"
 
 namespace {
 
@@ -182,8 +183,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     // by neighbouring tiles stay in that XCD's L2.
     const int tiles_m_or_listed = GROUPED ? *a.n_tiles : (a.M + BM - 1) / BM;
     const int total = tiles_m_or_listed * tiles_n;
-    // (a multiple of 4: bands of 2 or 4 row tiles stay on one XCD and in one round)
-    const int chunk = GROUPED ? (((total + 7) >> 3) + 3) & ~3 : (total + 7) >> 3;
+    int chunk = (total + 7) >> 3;
+    if constexpr (GROUPED) chunk = xcd_share(total, (int)gridDim.x >> 3);
     const int x_end = min(((int)blockIdx.x & 7) * chunk + chunk, total);
     const int stride = (int)gridDim.x >> 3;
     int L = ((int)blockIdx.x & 7) * chunk + ((int)blockIdx.x >> 3);
