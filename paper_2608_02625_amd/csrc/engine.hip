@@ -25,6 +25,7 @@
 
 #include "../../include/dlm.h"
 #include "kernels.h"
+#include "tiling.h"
 
 namespace {
 
@@ -395,54 +396,6 @@ GemmArgs gemm_args(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
     a.K = K;
     a.group_m = 4;
     return a;
-}
-
-// Tile of a dense product with M x N outputs of K products each.  The
-// ping-pong 256x256 tiles are the best per tile, but each is a CU's whole work
-// for a while: they are taken when their rounds over the 256 CUs are at least
-// three quarters full.  Below that, tiles of a quarter and a sixteenth of the
-// size, as many as two (or three) workgroups per CU hold at once.
-struct GemmTile {
-    int bm, bn, variant;
-};
-
-int64_t tiles_of(int64_t M, int64_t N, int bm, int bn) { return (M + bm - 1) / bm * ((N + bn - 1) / bn); }
-
-bool big_tiles_fill(int64_t M, int64_t N, int64_t K, double least) {
-    const int64_t n = tiles_of(M, N, 256, 256);
-    return K >= 2048 && n >= least * 256 * ((n + 255) / 256);
-}
-
-// Residual products (O, dense down), us with the launch, at d = K = 2048:
-// 512 rows (256 tiles of 64x64) 15.2 on 64x64 with five stages, 21.0 on 128x64,
-// 31.4 before; 1263 rows (640) 28.2 on 64x64 with three stages, 30.2 on 64x128,
-// 43.1 before; 2048 rows (1024) 30.6 on 128x128, 35.3 on 64x128, 37.2 before;
-// 5120 rows: 160 big tiles 59.7, 128x128 56.4; 8192 rows: 256 big tiles 74.4,
-// 128x128 78.3; 10240 rows: 320 big tiles 112, 128x128 92.6.  At K = 1024 a big
-// tile's epilogue weighs too much: 16384 rows (256 big tiles) 51.8 against 47.2.
-GemmTile resid_tile(int64_t M, int64_t N, int64_t K) {
-    if (big_tiles_fill(M, N, K, 0.8)) return {256, 256, 11};
-    const int64_t n = tiles_of(M, N, 64, 64);
-    if (n <= 512) return {64, 64, 3};
-    if (n <= 768) return {64, 64, 4};
-    return {128, 128, 3};
-}
-
-// QKV (M = features, N = tokens): d = 2048, 3072 features: 512 tokens (192
-// tiles of 128x64) 21.6, on 128x128 26.8, 256x128 (before) 40.9; 1263 (480)
-// 28.8 / 28.4 / 42.8; 2048 (768) 43.1 / 38.8 / 43.7; 6144 (288 big tiles) 106
-// against 88.1 on 128x128; 4096 (192 big) 58.5 against 60.6; 10240 (480 big)
-// 120 against 145.  With 4096-long rows 128x128 is ahead sooner: 512 tokens
-// (384 tiles of 128x64) 52.0 / 45.5 / 68.5.
-GemmTile qkv_tile(int64_t M, int64_t N, int64_t K) {
-    if (big_tiles_fill(M, N, K, 0.75)) return {256, 256, 11};
-    return tiles_of(M, N, 128, 64) <= (K < 4096 ? 512 : 256) ? GemmTile{128, 64, 3} : GemmTile{128, 128, 4};
-}
-
-// Gate/up of the dense FFN: M rows, N interleaved gate and up columns.
-GemmTile gate_up_tile(int64_t M, int64_t N, int64_t K) {
-    if (big_tiles_fill(M, N, K, 0.75)) return {256, 256, 11};
-    return tiles_of(M, N, 64, 128) <= 512 ? GemmTile{64, 128, 3} : GemmTile{128, 128, 3};
 }
 
 // Expert products of T tokens: what counts is the rows that an expert gets on

@@ -55,6 +55,28 @@ def test_rows_do_not_depend_on_the_batch(name, seq):
     log(f"[tiles {name} seq {seq}] batches {batches} equal the sequence alone")
 
 
+@pytest.mark.parametrize("over,seq,batch", [
+    # row counts that put O, dense down, QKV and gate/up on 256x256 tiles: K 2048
+    # in one round, K 1024 and 512 in several, and partly filled row tiles
+    (dict(d_model=2048, n_heads=16, n_kv_heads=4, head_dim=128, ffn_dim=2112), 64, 128),
+    (dict(d_model=1024, n_heads=16, n_kv_heads=4, head_dim=64, ffn_dim=4096), 64, 512),
+    (dict(d_model=1024, n_heads=8, n_kv_heads=2, head_dim=128, ffn_dim=3072), 61, 540),
+    (dict(d_model=512, n_heads=8, n_kv_heads=8, head_dim=64, ffn_dim=1024), 64, 1024),
+])
+def test_rows_of_large_calls(over, seq, batch):
+    """The same at the largest tiles: sequences of a large call equal the
+    sequence alone, bit for bit."""
+    need_gpu()
+    import torch
+    from paper_2608_02625_amd import Refiner
+    r = Refiner(dict(DENSE, **over), 5)
+    x = torch.randn(batch * seq, over["d_model"], generator=torch.Generator().manual_seed(batch)).cuda()
+    y = r.debug_layer(0, x.clone(), batch, seq)
+    for b in (0, 1, batch // 2, batch - 2, batch - 1):
+        lone = r.debug_layer(0, x[b * seq:(b + 1) * seq].clone(), 1, seq)
+        assert torch.equal(y[b * seq:(b + 1) * seq], lone), f"sequence {b}"
+
+
 @pytest.mark.parametrize("over,B,P,D", [
     # router with 2, 4 and 8 K parts, 2 and 4 expert blocks of 64, few and many tokens per group
     (dict(d_model=128, n_heads=2, n_kv_heads=2, head_dim=64, n_experts=256, top_k=1, expert_ffn_dim=64,
