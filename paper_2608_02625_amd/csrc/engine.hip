@@ -398,25 +398,6 @@ GemmArgs gemm_args(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
     return a;
 }
 
-// Expert products of T tokens: what counts is the rows that an expert gets on
-// average.  gate/up + down, us, at d 2048, 64 experts of 1024, top 8 (64x128 /
-// 128x128 / ping-pong tiles): 12 rows each 117 + 57 / 144 + 63 / 162 + 75; 64
-// rows 137 + 68 / 144 + 68 / 169 + 81; 80 rows 147 + 77 / 139 + 66 / 157 + 72;
-// 112 rows - / 140 + 70 / 165 + 78; 128 rows - / 165 + 86 / 168 + 82; 158 rows
-// - / 179 + 100 / 164 + 84.  An expert with more than 64 rows takes its weights
-// twice with 64-row tiles: with 257 groups of 25 MB (d 4096) that costs more
-// than the finer split gains (64 rows: 1438 + 790 / 1244 + 709 / 1230 + 672; 47
-// rows - / 1192 + 674 / 1205 + 646), so beyond 40 rows small tiles are for
-// models whose tiles are too few to even out otherwise.
-GemmTile expert_tile(const dlm_config& c, int64_t T) {
-    const int64_t G = c.n_experts + c.n_shared_experts;
-    const double rows = (double)T * c.top_k / c.n_experts;
-    const int64_t narrow = G * ((2 * (int64_t)c.expert_ffn_dim + 127) / 128);
-    if (rows <= 40 || (rows <= 72 && narrow <= 2048)) return {64, 128, 3};
-    if (rows <= (narrow <= 2048 ? 120 : 48)) return {128, 128, 3};
-    return {256, 256, 11};
-}
-
 #define TRY(expr)                        \
     do {                                 \
         dlm_status _s = (expr);          \
@@ -500,7 +481,7 @@ dlm_status run_layer(Ctx& x, int l) {
     int32_t* ids = x.at<int32_t>(x.w.ids);
     float* wts = x.at<float>(x.w.wts);
     int32_t* grp_off = x.at<int32_t>(x.w.grp_off);
-    const GemmTile et = expert_tile(c, Tf);
+    const GemmTile et = expert_tile(E + NS, F, (double)Tf * kk / E);
     const int rows_total = Tf * (kk + NS);
     const int max_tiles = std::min(rows_total, rows_total / et.bm + E + NS);
     // The table of smaller tiles is longer than the one of 256-row tiles, and

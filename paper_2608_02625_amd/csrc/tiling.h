@@ -94,3 +94,23 @@ constexpr GemmTile gate_up_tile(long long M, long long N, long long K) {
     if (b.fill >= (K < 512 ? 0.8 : K >= 1024 && b.rounds == 1 ? 0.51 : 0.67)) return {256, 256, 11};
     return tiles_of(M, N, 64, 128) <= 256 ? GemmTile{64, 128, 3} : GemmTile{128, 128, 3};
 }
+
+// Expert products of `groups` experts (shared ones among them) of ffn hidden
+// features: what counts is the rows that an expert gets on average.  gate/up +
+// down in us, d 2048, 64x128 / 128x128 / 256x256 tiles.  65 groups of 1024: 12
+// rows each 174 / 207 / 237; 64 rows 201 / 198 / 218; 96 rows 201 / 199 / 219;
+// 112 rows - / 210 / 243; 128 rows, two inputs, 254 / 226 / 238 and - / 251 / 250;
+// 158 rows - / 279 / 248.  96 of 768: 64 rows 187 / 196 / 210; 107 rows 233 / 217 / 224; 128 rows 286 / 254 / 237.
+// An expert with more rows than a tile takes its weights twice: with many
+// groups that costs more than the finer split gains.  128 of 768: 48 rows 225 /
+// 230 / 231; 64 rows 277 / 255 / 251; 96 rows 317 / 274 / 261.  161 of 1024: 38
+// rows 372 / 382 / 401; 51 rows 423 / 406 / 426; 77 rows 496 / 435 / 438.  257 of
+// 1536, d 4096: 47 rows - / 1866 / 1851; 64 rows 2228 / 1953 / 1902.  The line
+// between them, in gate/up tiles of 128 columns, lies between the 1152 of 96
+// groups of 768 and the 1536 of 128.
+constexpr GemmTile expert_tile(long long groups, long long ffn, double rows) {
+    const bool few = groups * ((2 * ffn + 127) / 128) <= 1280;
+    if (rows <= 40 || (few && rows <= 72)) return {64, 128, 3};
+    if (rows <= (few ? 120 : 48)) return {128, 128, 3};
+    return {256, 256, 11};
+}

@@ -15,6 +15,10 @@ WRAPPERS = """
 extern "C" int qkv(long long M, long long N, long long K) { const GemmTile t = qkv_tile(M, N, K); return t.bm * 1000 + t.bn; }
 extern "C" int resid(long long M, long long N, long long K) { const GemmTile t = resid_tile(M, N, K); return t.bm * 1000 + t.bn; }
 extern "C" int gate_up(long long M, long long N, long long K) { const GemmTile t = gate_up_tile(M, N, K); return t.bm * 1000 + t.bn; }
+extern "C" int expert(long long groups, long long ffn, double rows) {
+    const GemmTile t = expert_tile(groups, ffn, rows);
+    return t.bm * 1000 + t.bn;
+}
 extern "C" int share(int total, int workgroups) { return xcd_share(total, workgroups); }
 """
 
@@ -100,3 +104,24 @@ def test_small_gate_up_tiles(lib):
     for M, N, K, narrow, wide in GATE_UP_SMALL:
         mine = {64128: narrow, 128128: wide}[lib.gate_up(M, N, K)]
         assert mine <= 1.04 * min(narrow, wide), (M, N, K, mine, narrow, wide)
+
+
+# (groups, ffn, rows per expert, us of gate/up + down on 64x128, 128x128 and 256x256 tiles), d 2048, 8 experts per
+# token (65 and 161 groups: one of them shared)
+EXPERTS = [
+    (65, 1024, 16, 170.4, 191.7, 202.0), (65, 1024, 48, 179.9, 195.7, 212.9), (65, 1024, 64, 201.0, 198.3, 217.5),
+    (65, 1024, 96, 200.7, 199.3, 218.9), (65, 1024, 192, 341.3, 265.5, 253.3), (65, 1024, 512, 723.1, 558.6, 428.5),
+    (40, 1536, 64, 176.8, 179.5, 190.0), (40, 1536, 102, 212.2, 193.3, 204.4), (40, 1536, 205, 315.6, 249.6, 229.9),
+    (96, 768, 32, 182.2, 194.3, 205.6), (96, 768, 64, 186.6, 196.3, 209.7), (96, 768, 85, 235.6, 217.9, 225.3),
+    (96, 768, 107, 233.3, 217.7, 223.9), (96, 768, 128, 285.7, 253.6, 237.2), (128, 768, 24, 228.3, 227.0, 228.7),
+    (128, 768, 48, 224.5, 230.4, 230.9), (128, 768, 64, 277.2, 255.3, 251.4), (128, 768, 80, 278.6, 251.3, 248.6),
+    (128, 768, 96, 316.9, 273.7, 261.1), (161, 1024, 38, 372.3, 382.3, 400.9), (161, 1024, 77, 496.1, 435.2, 437.6),
+    (161, 1024, 102, 561.1, 492.3, 458.7),
+]
+
+
+def test_expert_tiles(lib):
+    lib.expert.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_double]
+    for groups, ffn, rows, *us in EXPERTS:
+        mine = us[[64128, 128128, 256256].index(lib.expert(groups, ffn, rows))]
+        assert mine <= 1.04 * min(us), (groups, ffn, rows, mine, us)
