@@ -69,29 +69,33 @@ __global__ void rmsnorm_draft_kernel(const float* __restrict__ x, const bf16_t* 
 }
 
 // Merge the per-vocabulary-tile partials of each row.  A workgroup handles 8
-// rows; each of the 128 thread groups of a row takes every 128th tile (online
+// rows; each of a row's GROUPS thread groups takes every GROUPS-th tile (online
 // merge in tile order; one read covers 8 consecutive rows = 128 contiguous
 // bytes), then the group results are merged as a tree through LDS.  The order
 // is fixed, so results are deterministic; ties keep the lower vocabulary id.
-// Each merge waits for two exponentials, so the chain is what counts: 1228
-// tiles over 32 groups, then one thread over the groups, took 21.2 us for 201
-// rows and 22.4 for 512.
-constexpr int kMergeGroups = 128;
-__global__ __launch_bounds__(8 * kMergeGroups) void lmhead_merge_kernel(const float4* __restrict__ part, int n_tiles, int R,
-                                                                        int32_t* __restrict__ top1, float* __restrict__ conf,
-                                                                        float* __restrict__ max_logit) {
-    __shared__ float4 red[kMergeGroups][8];
+// Each merge waits for two exponentials, so the chain is what counts.  With the
+// launch (6.4), 201 and 512 rows of 1228 tiles: 21.4 us each over 32 groups and
+// then one thread over the groups, 9.3 and 8.4 over 128 and the tree.  Up to 64
+// tiles 32 groups are enough (chains of two), and the idle ones of 128 cost:
+// 12288 rows of 16 tiles 6.7 against 11.2, of 64 tiles 7.8 against 11.9.  Two
+// tiles in a chain are added as the first level of the wider tree adds them, so
+// the bits are the same.
+template <int GROUPS>
+__global__ __launch_bounds__(8 * GROUPS) void lmhead_merge_kernel(const float4* __restrict__ part, int n_tiles, int R,
+                                                                  int32_t* __restrict__ top1, float* __restrict__ conf,
+                                                                  float* __restrict__ max_logit) {
+    __shared__ float4 red[GROUPS][8];
     const int rl = threadIdx.x & 7, split = threadIdx.x >> 3;
     const int r = blockIdx.x * 8 + rl;
     SoftmaxPartial acc{-INFINITY, 0x7fffffff, 0.f};
     if (r < R) {
 #pragma unroll 4
-        for (int t = split; t < n_tiles; t += kMergeGroups) {
+        for (int t = split; t < n_tiles; t += GROUPS) {
             const float4 p = part[(int64_t)t * R + r];
             acc = sp_merge(acc, SoftmaxPartial{p.x, __float_as_int(p.y), p.z});
         }
     }
-    for (int n = kMergeGroups; n > 1; n >>= 1) {      // groups 0 .. n-1 hold results; the upper half hands over
+    for (int n = GROUPS; n > 1; n >>= 1) {      // groups 0 .. n-1 hold results; the upper half hands over
         if (split < n && split >= n / 2) red[split][rl] = make_float4(acc.m, __int_as_float(acc.idx), acc.s, 0.f);
         __syncthreads();
         if (split < n / 2) {
@@ -305,8 +309,12 @@ void launch_rmsnorm_draft_rows(const float* x, const bf16_t* g, bf16_t* h, int B
 
 void launch_lmhead_merge(const float4* partials, int n_tiles, int R, int32_t* top1, float* conf,
                          float* max_logit, hipStream_t st) {
-    hipLaunchKernelGGL(lmhead_merge_kernel, dim3((R + 7) / 8), dim3(8 * kMergeGroups), 0, st, partials,
-                       n_tiles, R, top1, conf, max_logit);
+    if (n_tiles <= 64)
+        hipLaunchKernelGGL(lmhead_merge_kernel<32>, dim3((R + 7) / 8), dim3(8 * 32), 0, st, partials, n_tiles, R, top1,
+                           conf, max_logit);
+    else
+        hipLaunchKernelGGL(lmhead_merge_kernel<128>, dim3((R + 7) / 8), dim3(8 * 128), 0, st, partials, n_tiles, R, top1,
+                           conf, max_logit);
 }
 
 void launch_edit(int32_t* tokens, int B, int S, int P, int D, const int32_t* top1, const float* conf,
