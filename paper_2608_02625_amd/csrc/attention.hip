@@ -10,11 +10,11 @@
 // first n_keys rows of a longer per-layer K/V cache of Skv rows (everything up
 // to the window's end).  Every window query sees exactly those keys, which is
 // the block-causal mask for a window that is one block or the prompt.  A
-// window may also hold the finished block before the current one: its first
-// q_split query rows then see only the first n_keys_lo keys (up to their own
-// block's end), the others all n_keys.  Or it holds the prompt and several
-// blocks, or several blocks, each row seeing the keys up to its block's end
-// (`block`): limits grow with the row, so a workgroup stops at its last row's.
+// window may also hold the prompt before the first block: its first q_split
+// query rows then see only the first n_keys_lo keys (the prompt's own), the
+// others all n_keys.  Or it holds several blocks (`block`; never with q_split),
+// each row seeing the keys up to its block's end.  Limits grow with the row, so
+// a workgroup stops at its last row's.
 //
 // One workgroup = 4 waves = 128 queries of one (batch, head); each wave owns 32
 // queries.  Per tile of KEYS keys, K [KEYS][hd] and V^T [hd][KEYS] are copied
@@ -86,9 +86,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
     const int qb = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int kvh = h / (H / KV);
     const int q = qb * 128 + wave * 32 + j;
-    const int first = n_keys - (Sq - q_split);          // keys before the rows from q_split on
     auto limit = [&](int r) {                           // keys that row r sees
-        return r < q_split ? n_keys_lo : block ? min(n_keys, first + ((r - q_split) / block + 1) * block) : n_keys;
+        return r < q_split ? n_keys_lo : block ? min(n_keys, n_keys - Sq + (r / block + 1) * block) : n_keys;
     };
     const int lim = limit(q);
     const int VS = vt_stride(Skv);
@@ -289,8 +288,7 @@ hipError_t launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, 
     if (Sq <= 0 || n_keys <= 0 || n_keys > Skv) return hipErrorInvalidValue;
     if (q_split < 0 || q_split > Sq || (q_split > 0 && (n_keys_lo < 1 || n_keys_lo > n_keys)))
         return hipErrorInvalidValue;
-    // limits must not fall from one row to the next
-    if (block < 0 || (block > 0 && n_keys - (Sq - q_split) < (q_split > 0 ? n_keys_lo : 0))) return hipErrorInvalidValue;
+    if (block < 0 || (block > 0 && (q_split > 0 || n_keys < Sq))) return hipErrorInvalidValue;
     const dim3 grid((Sq + 127) / 128, H, B);
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)hd);
     // byte sizes of the K buffer (with its one-tile tail) and of V^T

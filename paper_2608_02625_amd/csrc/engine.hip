@@ -324,7 +324,7 @@ struct Ctx {
     bool kv_only = false;               // stop after the last layer's K/V (cache commit)
     bool no_events = false;             // no profiling events (the entry point allocates nothing)
     int att_split = 0, att_keys_lo = 0;  // window rows below att_split see only att_keys_lo keys
-    int att_block = 0;                  // > 0: the rows from there on are blocks that see no later one
+    int att_block = 0;                  // > 0: the window's rows are blocks that see no later one
     bool head_next = false;             // the head follows the last block
     bool hfin_ready = false;            // hfin already holds the head's normalised rows
     float* dbg_router_logits = nullptr;  // test hook: router logits [T][E] of the layer run
@@ -743,6 +743,8 @@ struct Drafter {
             x.att_split = prompt_rows;
             x.att_keys_lo = P;
         }
+        // Only without the prompt: after the prompt's rows a window of
+        // max(P, min(2 blk, D)) rows has room for one block at most.
         if (L - prompt_rows > blk) x.att_block = blk;
         int32_t* wtok = x.at<int32_t>(p.wtok);
         LAUNCH(x, "window_gather", launch_window_gather(tokens, wtok, B, S, c0, L, st));

@@ -85,10 +85,10 @@ hipError_t launch_gemm(const GemmArgs& a, int epi, bool grouped, int bm, int bn,
 // Draft windows: Q holds Sq rows per sequence, K and V^T hold Skv rows per
 // sequence of which the first n_keys are visible (n_keys <= Skv); O [B*Sq][H*hd].
 // With q_split > 0 the first q_split query rows see only the first n_keys_lo
-// keys (1 <= n_keys_lo <= n_keys).  With block > 0 the rows from q_split on are
-// blocks of that many positions, each seeing the keys up to its own end: row
-// q_split + i the first n_keys - (Sq - q_split) + (i / block + 1) * block of
-// them, at most n_keys (0: all n_keys).
+// keys (1 <= n_keys_lo <= n_keys).  With block > 0 (and q_split = 0) the rows are
+// the last Sq <= n_keys positions, in blocks of that many, each seeing the keys
+// up to its own block's end: row i the first n_keys - Sq + (i / block + 1) *
+// block of them, at most n_keys (0: all n_keys).
 hipError_t launch_attention(const bf16_t* q, const bf16_t* k, const bf16_t* v, bf16_t* o, int B,
                             int Sq, int Skv, int n_keys, int H, int KV, int hd, hipStream_t st, int q_split = 0,
                             int n_keys_lo = 0, int block = 0);
