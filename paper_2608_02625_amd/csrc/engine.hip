@@ -511,11 +511,11 @@ dlm_status run_layer(Ctx& x, int l) {
         // in the attention output's buffer too where it holds both; else groups
         // of 32, whose counts have a place of their own.
         const size_t tab_bytes = tab_in_attn ? align_up((size_t)max_tiles * 8) : 0;
-        int group = router_group_tokens(Tf, E, 8);
+        int group = router_group_tokens(Tf, 8);
         if (in_y && tab_bytes + (size_t)E * ((Tf + group - 1) / group) * 4 <= (size_t)Tf * H * hd * 2)
             wg_counts = x.at<int32_t>(x.w.attn + tab_bytes);
         else
-            group = router_group_tokens(Tf, E, 32);
+            group = router_group_tokens(Tf, 32);
         prof_begin(x, "router_logits");
         hipError_t e = launch_router_logits(h, x.wt(L.wr), Tf, d, E, n_split, parts, x.st);
         prof_end(x, "router_logits");

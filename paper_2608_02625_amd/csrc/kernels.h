@@ -166,7 +166,7 @@ hipError_t launch_router_logits(const bf16_t* h, const bf16_t* Wr, int T, int d,
 // wg_counts[E][ceil(T / group_tokens)] = per expert and workgroup selection
 // counts.  logits (may be null): the router logits float [T][E] (test hook).
 // router_group_tokens: group size to use, a multiple of `least`.
-int router_group_tokens(int T, int E, int least);
+int router_group_tokens(int T, int least);
 hipError_t launch_router_topk(const float* parts, int n_split, int T, int E, int k, int group_tokens, int32_t* ids,
                               float* w, int32_t* pos, int32_t* wg_counts, hipStream_t st, float* logits = nullptr);
 // Group row ranges (E routed + n_shared groups of T rows), tile table of the

@@ -139,10 +139,10 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
 // owner of that key (a ballot per expert block): k maxima of about 25
 // instructions each, where ranking every expert takes E compares per expert
 // owned.  Bound by those instructions.  Logits + top-k + dispatch against one
-// kernel of 32 tokens per workgroup that did both, us with each launch (4.4):
-// 10240 tokens, 256 experts, d 4096: 60 + 42 + 12 against 228 + 100; 640
-// tokens, 64 experts, d 2048: 6.5 + 6.4 + 7.2 against 21.5 + 7.2; 32768 tokens:
-// 40 + 31 + 13 against 84 + 114.
+// kernel of 32 tokens per workgroup that did both, us with each launch:
+// 10240 tokens, 256 experts, d 4096: 57 + 21 + 14 against 228 + 100; 640
+// tokens, 64 experts, d 2048: 6.2 + 6.2 + 6.7 against 21.5 + 7.2; 32768 tokens:
+// 40 + 29 + 14 against 84 + 114.
 // Lane r < k records selection r with its rank among this workgroup's
 // selections of the same expert (LDS counter), and the workgroup's per-expert
 // counts go to wg_counts[E][workgroup].  Ranks only order rows inside an
@@ -407,13 +407,16 @@ int router_splits(int T, int d, int E, int64_t capacity) {
 }
 
 // The top-k of a token is about 2000 cycles of a SIMD, so small groups spread
-// it (640 tokens of 64 experts: 20 groups of 32 take 6.4 us), but the dispatch
-// workgroups each read all groups' counts: at most 256 groups and 32768 counts
-// (at 32768 tokens of 64 experts, dispatch with the launch: 512 groups 45 us,
-// 256 groups 21; one workgroup planning 1024 groups, and a scatter: 116).
-int router_group_tokens(int T, int E, int least) {
-    const int64_t n = (T + least - 1) / least;
-    return least * (int)std::max<int64_t>((n + 255) / 256, (E * n + 32767) / 32768);
+// it, but the dispatch workgroups each read all groups' counts: at most 256
+// groups.  top-k + dispatch, us with each launch (5.9): 640 tokens of 64 experts
+// in groups of 8 (what run_layer asks for) 6.2 + 6.7, of 16 7.5 + 6.6, of 32 (its
+// fallback) 10.8 + 6.6; 5120 tokens of 64 experts in 128 / 256 / 512 groups 12.6 +
+// 7.8 / 9.5 + 8.2 / 9.6 + 9.5; 32768 in 128 / 256 / 512 / 1024 53 + 14 / 29 + 14 /
+// 24 + 14 / 22 + 23; 10240 tokens of 256 experts 37 + 11 / 21 + 14 / 18 + 26 / 17 +
+// 60.
+int router_group_tokens(int T, int least) {
+    const int64_t n = ((int64_t)T + least - 1) / least;
+    return least * (int)((n + 255) / 256);
 }
 
 hipError_t launch_router_logits(const bf16_t* h, const bf16_t* Wr, int T, int d, int E, int n_split, float* parts,
