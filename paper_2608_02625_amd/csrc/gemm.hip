@@ -73,8 +73,9 @@ __device__ __forceinline__ int swz(int row, int chunk) {
 
 // QKV projection, computed transposed: rows = q/k/v features, columns =
 // tokens.  A lane then holds, per accumulator, 4 consecutive features of one
-// token (8-byte stores into Q [B][H][S][hd] and K [B][KV][S][hd]; V goes to the
-// transposed layout V^T of kernels.h, consecutive lanes = consecutive keys).
+// token, and after an exchange of lane halves 16 (16-byte stores into Q
+// [B][H][S][hd] and K [B][KV][S][hd]; V goes to the transposed layout V^T of
+// kernels.h, consecutive lanes = consecutive keys).
 // The tile's rows take the features in units of 64 = a 32-feature block of a
 // head's first half followed by its RoPE partners (i + hd/2) from the second
 // half, so that the partners (rotate-half, applied in fp32 before rounding) are
@@ -334,7 +335,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4)
     const int fb0 = swz<CPR>(wn * T::WN + (lane & 31), lane >> 5);
     bf16x8 ra[T::KS][T::TM], rb[T::KS][T::TN];
     // Per-lane bases of the stages being read: fa_s = fa0 + stage * A_BYTES
-    // (the stage term sits above bit 14, so the slot XOR below commutes with it).
+    // (stages are whole rows of 64 or 128 bytes and ks * 32 stays below a row, so
+    // the slot XOR below commutes with the stage term).
     int fa_s = fa0, fb_s = B_BASE + fb0;
     auto set_stage = [&](int st_a, int st_b) {
         fa_s = fa0 + st_a * T::A_BYTES;

@@ -21,7 +21,9 @@ void launch_pass_setup(float2* tab, int S, int half, double theta, int P, int sh
 // to the 64-key attention tile.  Inside each aligned group of 16 keys the keys
 // are stored in the order an MFMA fragment consumes them: position of key s =
 // s with bits 2 and 3 exchanged (keys 4-7 and 8-11 of the group trade
-// places).  Positions of keys >= S are zero.
+// places).  Attention reads whole 32-key tiles: positions of keys >= S that such
+// a tile holds must be finite.  A refinement pass clears all of them, drafting
+// its whole caches where a block can end inside a tile.
 __host__ __device__ inline int vt_pos(int s) { return (s & ~12) | ((s & 4) << 1) | ((s & 8) >> 1); }
 __host__ __device__ inline int vt_stride(int S) { return (S + 63) & ~63; }
 
@@ -38,7 +40,7 @@ enum GemmEpilogue {
 
 // Row tiles of a group are listed in order, all of one height (a multiple of
 // 32 up to the tile's), and rastered in bands of at most this many; an entry is
-// (group | position in its band << 10 | row tiles of the band << 16 | height /
+// int2 (group | position in its band << 10 | row tiles of the band << 16 | height /
 // 32 << 22, first row in the group).
 constexpr int kRasterBand = 4;
 

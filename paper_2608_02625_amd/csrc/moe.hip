@@ -264,12 +264,13 @@ __device__ void wave_scan512(const int* in, int* out, int n) {
 // needs itself: every group's size (all routed experts, then n_shared shared
 // experts of T rows) and, per expert, how many of that expert's selections come
 // from router workgroups before w (1024 / (64 NQ) threads per expert row, E <=
-// 64 NQ, consecutive threads on consecutive counts, 16 loads at a time).  Workgroup 0 also writes grp_off, the tile table
-// (group, m0) of the grouped GEMM and its length.  The selections of the
-// workgroup's tokens then get their rows: slot (in place of the rank) =
-// grp_off[e] + those before w + rank, a_rows[slot] = token.  No workgroup waits
-// for another; every one reads the whole table, so the host makes the groups
-// large enough to keep it small (router_group_tokens).
+// 64 NQ, consecutive threads on consecutive counts, 16 loads at a time).
+// Workgroup 0 also writes grp_off, the tile table of the grouped GEMM (entries
+// as at kRasterBand) and its length.  The selections of the workgroup's tokens
+// then get their rows: slot (in place of the rank) = grp_off[e] + those before w
+// + rank, a_rows[slot] = token.  No workgroup waits for another; every one reads
+// the whole table, so the host makes the groups large enough to keep it small
+// (router_group_tokens).
 template <int NQ>
 __global__ __launch_bounds__(1024) void dispatch_kernel(const int32_t* __restrict__ ids, int T, int k, int E,
                                                        int n_shared, int nwg, int group_tokens, int bm,
