@@ -62,6 +62,8 @@ def test_rows_do_not_depend_on_the_batch(name, seq):
     (dict(d_model=1024, n_heads=16, n_kv_heads=4, head_dim=64, ffn_dim=4096), 64, 512),
     (dict(d_model=1024, n_heads=8, n_kv_heads=2, head_dim=128, ffn_dim=3072), 61, 540),
     (dict(d_model=512, n_heads=8, n_kv_heads=8, head_dim=64, ffn_dim=1024), 64, 1024),
+    # gate/up with fewer K tiles than stages
+    (dict(d_model=128, n_heads=4, n_kv_heads=2, head_dim=64, ffn_dim=1024), 64, 1024),
 ])
 def test_rows_of_large_calls(over, seq, batch):
     """The same at the largest tiles: sequences of a large call equal the

@@ -57,7 +57,7 @@ QKV = [
     (3072, 8192, 1024, 68.8, 64.2), (3072, 10240, 1024, 74.6, 83.2), (3072, 32768, 1024, 214.7, 251.8),
     (2304, 6144, 768, 34.6, 36.6), (2304, 16384, 768, 87.0, 77.3), (2304, 65536, 768, 263.4, 321.3),
     (1536, 16384, 512, 48.8, 41.6), (1536, 32768, 512, 76.1, 79.8), (768, 32768, 256, 39.6, 32.1),
-    (768, 65536, 256, 56.0, 58.1),
+    (768, 65536, 256, 56.0, 58.1), (1152, 65536, 384, 102.4, 99.8), (512, 65536, 128, 41.0, 36.8),
 ]
 RESID = [
     (6144, 2048, 2048, 59.3, 59.6), (8192, 2048, 2048, 73.1, 78.5), (10240, 2048, 2048, 112.3, 94.2),
@@ -79,6 +79,7 @@ GATE_UP = [
     (2111, 8192, 1024, 49.2, 43.5), (32768, 8192, 1024, 435.2, 551.5), (2048, 4096, 512, 17.5, 15.2),
     (4096, 4096, 512, 21.9, 23.6), (5120, 4096, 512, 30.3, 27.5), (6144, 4096, 512, 30.8, 32.6),
     (6144, 2048, 256, 14.6, 14.0), (20480, 2048, 256, 30.4, 32.2), (32768, 2048, 256, 40.9, 47.0),
+    (24576, 1024, 128, 20.1, 19.1), (65536, 2048, 128, 63.1, 70.0),
 ]
 # gate/up on (64x128, 128x128)
 GATE_UP_SMALL = [
