@@ -26,7 +26,7 @@ METRIC = "refined positions/sec per refinement step (1 GPU); MFMA % of bf16 peak
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gemm_expert_gate_up_mini_moe_hbm_traffic.md")
-GEMM_SOURCES = ("gemm.hip", "common.h", "kernels.h", "engine.hip")
+GEMM_SOURCES = ("gemm.hip", "common.h", "kernels.h", "tiling.h", "engine.hip")
 
 
 def kernel_source_digest():
