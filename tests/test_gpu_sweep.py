@@ -28,7 +28,7 @@ from workloads.inputs import draw_tokens
 
 pytestmark = pytest.mark.gpu
 
-# The committed sweep runs 16 cases; DLM_SWEEP_CASES widens it for a longer
+# The committed sweep runs 48 cases; DLM_SWEEP_CASES widens it for a longer
 # one-off run (the cases are the same seeded draws, extended).
 N_CASES = int(os.environ.get("DLM_SWEEP_CASES", "48"))
 # Larger shapes (more K tiles, more experts and tokens per case), fewer of them.
